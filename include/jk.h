@@ -103,13 +103,16 @@ typedef struct jk_batch jk_batch;
 /* Statistics of a plan (host copy). */
 typedef struct {
     int64_t nquartets;          /* significant unique shell quartets */
-    int64_t nprim_quartets;     /* primitive quartets inside them */
+    int64_t nprim_quartets;     /* primitive quartets inside them, by the shells'
+                                   contraction lengths */
     int64_t nquartets_fp32;     /* quartets the last build ran in FP32 (JK_MIXED: those
                                    below the threshold; JK_FP32: all evaluated) */
     int32_t nclasses;           /* (bra pair type, ket pair type) launches */
     int32_t npairs;             /* shell pairs kept after screening */
     double setup_ms;            /* jk_plan_create wall time */
-    double model_flops;         /* algorithmic FLOPs of one build with nset = 1 */
+    double model_flops;         /* algorithmic FLOPs of one build with nset = 1, over the
+                                   primitive quartets that are evaluated (those whose pairs
+                                   are above 2^-54 of their contracted pair) */
     int64_t nquartets_evaluated; /* quartets the last build evaluated (nquartets less
                                     those dropped by density screening) */
 } jk_stats;

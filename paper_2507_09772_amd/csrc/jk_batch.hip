@@ -326,8 +326,7 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                 a.ket_list = c.d_ket;
                 a.same = c.same;
                 a.npb = c.npb;
-                a.npk = c.npk;
-                a.nq = (int32_t)c.nq;
+                        a.nq = (int32_t)c.nq;
                 a.tpos = P->d_tpos;
                 a.aoc = P->maps.aoc;
                 a.D = md.Dc;

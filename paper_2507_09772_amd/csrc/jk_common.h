@@ -34,7 +34,8 @@ JK_HD constexpr int cart_comp(int l, int idx, int axis) {
 struct PairRec {
     int32_t ish, jsh;      // shell indices
     int32_t aoi, aoj;      // Cartesian AO offsets
-    int32_t pp_off, npp;   // first primitive pair, count
+    int32_t pp_off, npp;   // first primitive pair, count (those that matter in
+                           // double precision, largest first)
     int32_t pp_stride;     // distance between its consecutive primitive pairs
                            // (= the number of pairs of its type)
     int32_t jp_off;        // its first element in the pair-ordered J' buffer;
@@ -119,7 +120,8 @@ struct JkArgs {
     const PrimPair *pp;
     // JK mode: tiles over (bra list position, ket chunk)
     const int32_t *bra_list, *ket_list, *bra_cnt, *tile_off;
-    int32_t nbra, ntiles, same, npb, npk;
+    int32_t nbra, ntiles, same;
+    int32_t npb;  // most primitive pairs of a bra (LDS of the row kernels)
     // EXPORT mode: explicit quartets
     const int32_t *q_bra, *q_ket;
     int32_t nq;

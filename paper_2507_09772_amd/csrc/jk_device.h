@@ -500,6 +500,12 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+__device__ __forceinline__ int wave_max(int v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, 64));
+    return v;
+}
+
 // Largest i in [0, n) with off[i] <= key (off ascending, off[0] = 0).
 __device__ __forceinline__ int tile_bra(const int32_t *__restrict__ off, int n, int key) {
     int lo = 0, hi = n - 1;
@@ -731,7 +737,17 @@ __device__ __forceinline__ void k1_compute_op(const JkArgs &a, const PairRec &B,
     const R ab[3] = {(R)B.ab[0], (R)B.ab[1], (R)B.ab[2]};
     const R cd[3] = {(R)Kt.ab[0], (R)Kt.ab[1], (R)Kt.ab[2]};
     // ket primitive outer (one vector load each), bra primitive inner (the
-    // bra is uniform across a tile or row task)
+    // bra is uniform across a tile or row task).  The lanes' kets hold
+    // different numbers of primitive pairs: the loop runs, uniform in the
+    // wave, while any lane has one left, and a lane past its own repeats its
+    // last with weight zero (as a divergent loop the compiler kept more
+    // values live and spilled up to 1.8 KB more per lane).
+    auto ket_prim = [&](int ik) {
+        PrimPair r = a.pp[Kt.pp_off + min(ik, npk - 1) * Kt.pp_stride];
+        if (ik >= npk) r.kp = 0.0;
+        return r;
+    };
+    auto more = [&](int ik) { return __ballot(ik < npk) != 0ull; };
     if constexpr (!RS && RootPipe<NR, R>::ok) {
         // the root table row of the next primitive quartet is loaded while
         // the current one's recurrences run
@@ -741,11 +757,12 @@ __device__ __forceinline__ void k1_compute_op(const JkArgs &a, const PairRec &B,
         // (the one-root classes load each ket record when they reach it:
         // their registers, not the load, bound them)
         constexpr bool PREF = NR > 1;
-        PrimPair pk = a.pp[Kt.pp_off];
+        PrimPair pk = ket_prim(0);
         settle(pk);
-        for (int ik = 0; ik < npk; ++ik) {
+        for (int ik = 0;;) {
+            const bool next = more(ik + 1);
             PrimPair pkn;
-            if (PREF && ik + 1 < npk) pkn = a.pp[Kt.pp_off + (ik + 1) * Kt.pp_stride];
+            if (PREF && next) pkn = ket_prim(ik + 1);
             PT<R> t = prim_T<R>(pbat(0), pk);
             typename P::Row row;
             P::fetch(t.T, a.tab, row);
@@ -759,20 +776,20 @@ __device__ __forceinline__ void k1_compute_op(const JkArgs &a, const PairRec &B,
                 }
                 k1_roots_acc<LI, LJ, LK, LL, R>(g, u, w, ab, cd, V);
             }
-            if (ik + 1 < npk) {
-                if constexpr (PREF) {
-                    settle(pkn);
-                    pk = pkn;
-                } else {
-                    pk = a.pp[Kt.pp_off + (ik + 1) * Kt.pp_stride];
-                }
+            ++ik;
+            if (!next) break;
+            if constexpr (PREF) {
+                settle(pkn);
+                pk = pkn;
+            } else {
+                pk = ket_prim(ik);
             }
         }
         return;
     }
     const int vb = RS ? variant_begin(a.omega) : 0, ve = RS ? variant_end(a.omega) : 1;
-    for (int ik = 0; ik < npk; ++ik) {
-        const PrimPair pk = a.pp[Kt.pp_off + ik * Kt.pp_stride];
+    for (int ik = 0; more(ik); ++ik) {
+        const PrimPair pk = ket_prim(ik);
         for (int ib = 0; ib < npb; ++ib) {
             const PQuart<R> g = prim_quartet<R>(pbat(ib), pk);
             for (int var = vb; var < ve; ++var) {
@@ -802,7 +819,7 @@ __device__ __forceinline__ void k1_body(const JkArgs &a, int bra, int ket, bool 
     const PairRec Kt = a.pairs[ket];
     R V[C::NC];
     k1_compute<LI, LJ, LK, LL, R>(a, B, Kt, [&](int ib) { return a.pp[B.pp_off + ib * B.pp_stride]; },
-                                  BRA_UNIFORM ? a.npb : B.npp, MODE == MODE_JK ? a.npk : Kt.npp, V);
+                                  B.npp, Kt.npp, V);
     if constexpr (MODE == MODE_EXPORT) {
         if (valid) {
             double *o = a.out + gout * (NAB * NCD);
@@ -1032,7 +1049,7 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, int task) {
     const int dper = (NI + NJ) * ncols;
     double *drows = rows + (size_t)per_set * a.nset;
     const int n = a.nao;
-    for (int t = tid; t < a.npb; t += NT) sbra[t] = a.pp[B.pp_off + t * B.pp_stride];
+    for (int t = tid; t < B.npp; t += NT) sbra[t] = a.pp[B.pp_off + t * B.pp_stride];
     for (int t = tid; t < per_set * a.nset; t += NT) rows[t] = 0.0;
     if (dstage) {
         for (int t = tid; t < dper * a.nset; t += NT) {
@@ -1059,7 +1076,7 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, int task) {
         if (nv == 0) continue;
         evaluated += nv;
         R V[C::NC];
-        k1_compute<LI, LJ, LK, LL, R>(a, B, Kt, [&](int ib) { return sbra[ib]; }, a.npb, a.npk, V);
+        k1_compute<LI, LJ, LK, LL, R>(a, B, Kt, [&](int ib) { return sbra[ib]; }, B.npp, Kt.npp, V);
         const int cK = a.tpos[Kt.ish] * NK, cL = segL + a.tpos[Kt.jsh] * NL;
         for (int s = 0; s < a.nset; ++s) {
             const double *D = a.D + s * a.mstride;
@@ -1328,12 +1345,9 @@ __device__ __forceinline__ void k2_body(const JkArgs &a, R *tabs, double *dig, i
     const int qq = lane_used ? q : 0;
     const PairRec B = a.pairs[bra];
     const PairRec Kt = a.pairs[ket];
-    const int npb = MODE == MODE_JK ? a.npb : B.npp;
-    const int npk = MODE == MODE_JK ? a.npk : Kt.npp;
-    const int npq = npb * npk;
-    int npq_max = npq;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) npq_max = max(npq_max, __shfl_xor(npq_max, off, 64));
+    const int npb = B.npp;
+    const int npq = npb * Kt.npp;
+    const int npq_max = wave_max(npq);
 
     R *tq = tabs + qq * F::TAB;
     double *dq = dig + qq * F::DIG;
@@ -1874,7 +1888,10 @@ __global__ void __launch_bounds__(NT) jk_k3_row(const JkArgs a_in, const BatchDe
 #pragma unroll
         for (int e = 0; e < F::NV; ++e) V[e] = (R)0;
         const int vb = variant_begin(a.omega), nvar = variant_end(a.omega) - vb;
-        const int nit = a.npb * a.npk * nvar;
+        // the quartets of a wave hold different numbers of primitive pairs:
+        // the loop runs to the largest, a quartet past its own adds zeros
+        const int nmine = B.npp * Kt.npp * nvar;
+        const int nit = __builtin_amdgcn_readfirstlane(wave_max(nmine));
         R *gq = gt + qq * F::GQ;
         for (int it0 = 0; it0 < nit; it0 += PB) {
             wave_sync();
@@ -1885,8 +1902,9 @@ __global__ void __launch_bounds__(NT) jk_k3_row(const JkArgs a_in, const BatchDe
                 const int p = t / NR, r = t - p * NR;
                 const int it = it0 + p;
                 if (it >= nit) break;
-                const int ipq = it / nvar, var = vb + it % nvar;
-                const int ib = ipq % a.npb, ik = ipq / a.npb;
+                const bool has = it < nmine;
+                const int ipq = has ? it / nvar : 0, var = vb + it % nvar;
+                const int ib = ipq % B.npp, ik = ipq / B.npp;
                 const PQuart<R> g = prim_quartet<R>(a.pp[B.pp_off + ib * B.pp_stride], a.pp[Kt.pp_off + ik * Kt.pp_stride]);
                 R u, w;
                 rys_root1_op<NR, R>(g.T, g.rho, a.omega, var, r, a.tab, u, w);
@@ -1898,7 +1916,7 @@ __global__ void __launch_bounds__(NT) jk_k3_row(const JkArgs a_in, const BatchDe
                 for (int x = 0; x < 3; ++x) {
                     const R c00 = g.PA[x] - g.fq * u * g.PQ[x];
                     const R c00p = g.QC[x] + g.fp * u * g.PQ[x];
-                    vrr2d<F::NA, NCC, R>(c00, c00p, b00, b10, b01, x == 2 ? w * g.pref : (R)1, dst + x * F::GS);
+                    vrr2d<F::NA, NCC, R>(c00, c00p, b00, b10, b01, x == 2 ? (has ? w * g.pref : (R)0) : (R)1, dst + x * F::GS);
                 }
             }
             wave_sync();
