@@ -265,22 +265,43 @@ __global__ void k_det_collapse(double *p, int64_t L, int64_t n) {
     }
 }
 
-__global__ void k_jp_scatter(const PairRec *pairs, const int32_t *lsh, const double *jp, int64_t jpstride, double *Jc,
-                             int64_t mstride, int naoc, int npair, int64_t nt) {
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < nt; t += (int64_t)gridDim.x * blockDim.x)
-        jp_scatter_elem(pairs, lsh, jp, jpstride, Jc, mstride, naoc, npair, t);
-}
-
 __global__ void k_fill(double *p, int64_t n, double v) {
     for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) p[t] = v;
 }
 
 
-// Dc[s][a][b] = sum_{m, n} T_I[m][a] D[s][m][n] T_J[n][b]  (D spherical)
-__global__ void k_sph_to_cart(AoMaps m, const double *D, double *Dc, int nao, int naoc, int nset) {
-    const int64_t tot = (int64_t)nset * naoc * naoc;
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x)
-        Dc[t] = sph_to_cart_elem(m, D, nao, naoc, t);
+// Before the class kernels, in one launch: Dc = T^T D T (spherical bases; else
+// Dc is NULL) and zeros in J', K', the pair-ordered J' and the counters.
+__global__ void k_prepare(AoMaps m, const double *D, double *Dc, int nao, int naoc, int nset, double *Jc, double *Kc,
+                          double *jp, int64_t njp, unsigned long long *ctr, int nctr) {
+    const int64_t tot = (int64_t)nset * naoc * naoc, t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t t = t0; t < tot; t += step) {
+        if (Dc) Dc[t] = sph_to_cart_elem(m, D, nao, naoc, t);
+        if (Jc) Jc[t] = 0.0;
+        if (Kc) Kc[t] = 0.0;
+    }
+    if (jp)
+        for (int64_t t = t0; t < njp; t += step) jp[t] = 0.0;
+    for (int64_t t = t0; t < nctr; t += step) ctr[t] = 0ull;
+}
+
+// After the class kernels, in one launch: the pair-ordered J' into J' (blocks
+// 0 .. nbs - 1) and K = T (K' + K'^T) T^T (the other blocks).
+__global__ void k_scatter_finalize(const PairRec *pairs, const double *jp, int64_t jpstride, double *Jc, int npair,
+                                   int64_t nt, int nbs, AoMaps m, const double *Kc, double *K, int nao, int naoc, int nset,
+                                   int spherical, int accumulate) {
+    if ((int)blockIdx.x < nbs) {
+        const int64_t mstride = (int64_t)naoc * naoc;
+        for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < nt; t += (int64_t)nbs * blockDim.x)
+            jp_scatter_elem(pairs, m.l, jp, jpstride, Jc, mstride, naoc, npair, t);
+        return;
+    }
+    const int64_t tot = (int64_t)nset * nao * nao, step = (int64_t)(gridDim.x - nbs) * blockDim.x;
+    for (int64_t t = (blockIdx.x - nbs) * (int64_t)blockDim.x + threadIdx.x; t < tot; t += step) {
+        const double v = finalize_elem(m, Kc, nao, naoc, spherical, t);
+        K[t] = accumulate ? K[t] + v : v;
+    }
 }
 
 // out[s] (+)= T (X + X^T) T^T, or X + X^T for Cartesian bases
@@ -380,7 +401,7 @@ static double flops_digest(int li, int lj, int lk, int ll) {
 static int launch_export(jk_plan *P, int li, int lj, int lk, int ll, int precision, const int32_t *d_qb, const int32_t *d_qk,
                          int nq, double *d_out, hipStream_t s) {
     const ClassEntry &e = g_classes[class_id(li, lj, lk, ll)];
-    Launcher f = precision == JK_FP64 ? e.ex64 : e.ex32;
+    ExportLauncher f = precision == JK_FP64 ? e.ex64 : e.ex32;
     if (!f) return fail(JK_EUNSUPPORTED, "class (%d%d|%d%d) not built", li, lj, lk, ll);
     JkArgs a{};
     a.pairs = P->d_pairs;
@@ -392,6 +413,59 @@ static int launch_export(jk_plan *P, int li, int lj, int lk, int ll, int precisi
     a.tab = P->tab;
     HIPCHK(f(a, s));
     return 0;
+}
+
+// The classes' argument blocks on the device, and the classes of each
+// angular class (launched together), longest primitive loops first so that
+// the long workgroups of a launch start early.
+static int place_classes(jk_plan *P) {
+    std::vector<ClsArgs> ca(8 * P->cls.size());
+    std::vector<int> of(NCLS, -1);
+    std::vector<double> flops;
+    for (size_t ci = 0; ci < P->cls.size(); ++ci) {
+        const ClassTask &c = P->cls[ci];
+        for (int pr = 0; pr < 2; ++pr) {
+            const int f = c.fam[pr], ft = f == 3 ? tile_fallback(c.li, c.lj, c.lk, c.ll) : f;
+            ClsArgs b{};
+            b.ket_list = c.d_ket;
+            b.npb = c.npb;
+            b.tshK = c.d_tshK;
+            b.tshL = c.d_tshL;
+            b.ncolK = c.ncolK;
+            b.ncolL = c.ncolL;
+            b.seg_same = c.seg_same;
+            b.bra_list = c.d_bra;
+            b.bra_cnt = c.d_cnt;
+            b.nbra = c.nbra;
+            b.tile_off = c.d_tile[ft - 1];
+            b.ctr = work_slot(ci, pr, WORK_TILES);
+            ca[work_slot(ci, pr, WORK_TILES)] = b;
+            b.ctr = work_slot(ci, pr, WORK_ROWS);
+            b.row_pos = c.d_rowc[f - 1];
+            ca[work_slot(ci, pr, WORK_ROWS)] = b;
+            b.ctr = work_slot(ci, pr, WORK_SROWS);
+            b.row_pos = c.d_srowt;
+            ca[work_slot(ci, pr, WORK_SROWS)] = b;
+            b.row_pos = nullptr;
+            b.bra_list = c.d_sbra;
+            b.bra_cnt = c.d_scnt;
+            b.nbra = c.nsbra;
+            b.tile_off = c.d_stile[ft - 1];
+            b.ctr = work_slot(ci, pr, WORK_TILES);
+            ca[work_slot(ci, pr, WORK_STILES)] = b;
+        }
+        int &k = of[class_id(c.li, c.lj, c.lk, c.ll)];
+        if (k < 0) {
+            k = (int)P->ang.size();
+            P->ang.emplace_back();
+        }
+        P->ang[k].push_back((int)ci);
+    }
+    for (auto &v : P->ang)
+        std::stable_sort(v.begin(), v.end(), [&](int x, int y) {
+            return P->cls[x].npb * P->cls[x].npk > P->cls[y].npb * P->cls[y].npk;
+        });
+    return P->put(&P->d_cls, ca);
 }
 
 extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **out) {
@@ -745,6 +819,8 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
     // heaviest classes first
     std::stable_sort(P->cls.begin(), P->cls.end(), [](const ClassTask &a, const ClassTask &b) { return a.flops > b.flops; });
 
+    if ((rc = place_classes(P))) return rc;
+
     // AO maps for the spherical transforms
     std::vector<int32_t> shc(P->naoc), cc(P->naoc), she(P->nao), ce(P->nao);
     for (int i = 0; i < ns; ++i) {
@@ -1097,20 +1173,13 @@ int execute_impl(jk_plan *P, const double *D, int32_t nset, int32_t flags, int32
     double *const Kc = det ? sc.det + 3 * sc.detL : sc.Kc;
     double *const jpb = det ? sc.det + 6 * sc.detL : sc.jp;
     const double *Dc = D;
-    if (P->sph) {
-        hipLaunchKernelGGL(k_sph_to_cart, dim3(grid_for((int64_t)nset * m, 256)), dim3(256), 0, s, P->maps, D, sc.Dc, P->nao, P->naoc, nset);
-        HIPCHK(hipGetLastError());
-        Dc = sc.Dc;
-    }
-    if (det) {
-        hipLaunchKernelGGL(k_fill, dim3(grid_for(9 * sc.detL, 256)), dim3(256), 0, s, sc.det, 9 * sc.detL, 0.0);
-    } else {
-        hipLaunchKernelGGL(k_fill, dim3(grid_for((int64_t)nset * m, 256)), dim3(256), 0, s, Jc, (int64_t)(nset * m), 0.0);
-        hipLaunchKernelGGL(k_fill, dim3(grid_for((int64_t)nset * m, 256)), dim3(256), 0, s, Kc, (int64_t)(nset * m), 0.0);
-        hipLaunchKernelGGL(k_fill, dim3(grid_for((int64_t)nset * P->njp, 256)), dim3(256), 0, s, jpb, (int64_t)nset * P->njp, 0.0);
-    }
     const int nctr = (int)scratch_sizes(P, nset).nsel;
-    hipLaunchKernelGGL(k_fill_u64, dim3((nctr + 255) / 256), dim3(256), 0, s, sc.nsel, nctr);
+    const int64_t njp = (int64_t)nset * P->njp;
+    if (P->sph) Dc = sc.Dc;
+    if (det) hipLaunchKernelGGL(k_fill, dim3(grid_for(9 * sc.detL, 256)), dim3(256), 0, s, sc.det, 9 * sc.detL, 0.0);
+    hipLaunchKernelGGL(k_prepare, dim3(grid_for(std::max<int64_t>({(int64_t)(nset * m), njp, nctr}), 256)), dim3(256), 0, s,
+                       P->maps, D, P->sph ? sc.Dc : nullptr, P->nao, P->naoc, nset, det || !do_j ? nullptr : Jc,
+                       det || !do_k ? nullptr : Kc, det || !do_j ? nullptr : jpb, njp, sc.nsel, nctr);
     HIPCHK(hipGetLastError());
     if (precision == JK_MIXED || P->dscreen > 0.0) {
         hipLaunchKernelGGL(k_dmax, dim3((P->ns * P->ns + 255) / 256), dim3(256), 0, s, Dc, P->maps.aoc, P->maps.l, P->ns, P->naoc, nset, sc.dmax);
@@ -1145,15 +1214,92 @@ int execute_impl(jk_plan *P, const double *D, int32_t nset, int32_t flags, int32
     // with every quartet selected and no density screening a launch
     // evaluates exactly its quartets: no device counting
     const bool count_on_device = precision == JK_MIXED || P->dscreen > 0.0;
-    auto set_count = [&](int slot, int64_t host_count) {
-        a.nsel = count_on_device ? sc.nsel + (size_t)slot * NSEL_SLOTS * NSEL_STRIDE : nullptr;
-        P->last_fixed[slot] = count_on_device ? -1 : host_count;
-    };
+    a.nsel = count_on_device ? sc.nsel : nullptr;
+    a.dstage = P->no_dstage ? 0 : 1;
     const bool profile = P->profile && allow_profile;
-    // launches in order: timing slot of each
-    std::vector<int> slots;
+    // the launches of the build: the classes of one angular class together,
+    // one launch per kernel (tiles, long rows, short rows; per precision),
+    // rows apart where their LDS would cost the others workgroups per CU.
+    // Timed builds launch every class by itself.
+    struct Launch {
+        Launcher fn;
+        size_t lds;
+        int sel, slot;  // quartet selection; counter slot (timed builds)
+        double flops;
+        ClsGroup g;
+    };
+    std::vector<Launch> launches;
+    launches.reserve(profile ? 4 * P->cls.size() : 64);
+    for (const std::vector<int> &v : P->ang) {
+        const ClassTask &c0 = P->cls[v[0]];
+        const ClassEntry &e = g_classes[class_id(c0.li, c0.lj, c0.lk, c0.ll)];
+        // mixed: a single-precision pass over the quartets below the
+        // threshold and a double-precision pass over the rest; both walk
+        // the class's tiles and row tasks
+        const bool msplit = precision == JK_MIXED && c0.split;  // (else the class runs in FP64)
+        for (int pass = 0; pass < (msplit ? 2 : 1); ++pass) {
+            const int pr = msplit ? (pass == 0 ? 1 : 0) : (precision == JK_FP32 ? 1 : 0);
+            const int sel = msplit ? (pass == 0 ? SEL_LO : SEL_HI) : SEL_ALL;
+            const int f = c0.fam[pr];
+            // tiles (the short rest) of family 3 classes run in the fallback family
+            const int ft = f == 3 ? tile_fallback(c0.li, c0.lj, c0.lk, c0.ll) : f;
+            // the double-precision pass of the mixed split runs as tiles: its
+            // quartets are the first few kets of each bra (largest Schwarz
+            // factors), a fraction of one row-mode pass per bra, and tiles
+            // past them end at their first ket
+            // (and every class in the fixed-order mode: the row kernels add
+            // into their LDS rows from several waves, in no fixed order)
+            const bool tiles_only = sel == SEL_HI || det || P->no_row;
+            const size_t first = launches.size();
+            auto add = [&](Launcher fn, size_t ci, int kind, int units, size_t lds, int64_t nq) {
+                const int slot = work_slot(ci, pr, kind == WORK_STILES ? WORK_TILES : kind);
+                P->last_fixed[slot] = count_on_device ? -1 : nq;
+                const int wgs = lds ? std::min(8, (int)(160 * 1024 / lds)) : 0;
+                size_t k = first;
+                if (profile) k = launches.size();
+                while (k < launches.size() &&
+                       !(launches[k].fn == fn && launches[k].g.n < GROUP_MAX &&
+                         (lds == 0 || wgs == std::min(8, (int)(160 * 1024 / launches[k].lds))) &&
+                         launches[k].g.base[launches[k].g.n] <= INT32_MAX - units))
+                    ++k;
+                if (k == launches.size()) {
+                    launches.emplace_back();
+                    launches[k].fn = fn;
+                    launches[k].sel = sel;
+                    launches[k].slot = slot;
+                }
+                Launch &l = launches[k];
+                l.lds = std::max(l.lds, lds);
+                l.g.desc[l.g.n] = work_slot(ci, pr, kind);
+                l.g.base[l.g.n + 1] = l.g.base[l.g.n] + units;
+                ++l.g.n;
+                l.flops += P->cls[ci].flops * (double)nq / (double)P->cls[ci].nq;
+            };
+            for (int ci : v) {
+                const ClassTask &c = P->cls[ci];
+                const int ncols = c.ncolK + (c.seg_same ? 0 : c.ncolL);
+                const size_t lds4 = row_lds_bytes(e, f, pr, c.li, c.lj, nset, ncols, 4, c.npb);
+                const size_t lds1 = row_lds_bytes(e, f, pr, c.li, c.lj, nset, ncols, 1, c.npb);
+                const bool longrows = !tiles_only && c.row_ok[pr] && c.nrow > 0 && e.row[f - 1][pr] && lds4 <= (size_t)ROW_LDS_MAX;
+                const bool shortrows = !tiles_only && c.row_short[pr] && c.nsrow > 0 && e.srow[f - 1][pr] &&
+                                       (longrows || c.nrow == 0) && lds1 <= (size_t)ROW_LDS_MAX;
+                // long bras: 256-lane workgroups over chunks of their kets
+                // (family 1 with the bra's D rows in LDS where they fit)
+                const bool dst = a.dstage && f == 1 && k1_dstage(c.li, c.lj, nset, ncols, c.npb);
+                if (longrows)
+                    add(e.row[f - 1][pr], ci, WORK_ROWS, c.nrowc[f - 1],
+                        dst ? k1_row_lds(c.li, c.lj, nset, ncols, c.npb, true) : lds4, c.nq_row);
+                // short bras: one 64-lane workgroup each, or tiles
+                const int64_t nq = longrows ? c.nq - c.nq_row : c.nq;
+                if (shortrows) add(e.srow[f - 1][pr], ci, WORK_SROWS, c.nsrow, lds1, c.nq - c.nq_row);
+                else if (longrows && c.nstiles[ft - 1] > 0) add(e.tiles[ft - 1][pr], ci, WORK_STILES, c.nstiles[ft - 1], 0, nq);
+                else if (!longrows && c.ntiles[ft - 1] > 0) add(e.tiles[ft - 1][pr], ci, WORK_TILES, c.ntiles[ft - 1], 0, nq);
+            }
+        }
+    }
+    // timed builds: an event before every launch, on s
     int nev = 0;
-    auto mark = [&](int slot) -> int {
+    auto mark = [&]() -> int {
         if (!profile) return 0;
         if ((int)P->events.size() <= nev) {
             hipEvent_t ev;
@@ -1161,13 +1307,14 @@ int execute_impl(jk_plan *P, const double *D, int32_t nset, int32_t flags, int32
             P->events.push_back(ev);
         }
         HIPCHK(hipEventRecord(P->events[nev++], s));
-        if (slot >= 0) slots.push_back(slot);
         return 0;
     };
-    // the class launches only add into Jc, Kc and jp with atomics, so
-    // classes may overlap: each class goes whole to the least loaded of the
-    // plan's streams (by model flops), forked from s and joined back into s
+    // the class launches only add into Jc, Kc and jp with atomics, so they
+    // may overlap: each goes to the least loaded of the plan's streams (by
+    // model flops, heaviest first), forked from s and joined back into s
     // before the J'_KL scatter. Timed builds stay on s.
+    if (!profile)
+        std::stable_sort(launches.begin(), launches.end(), [](const Launch &x, const Launch &y) { return x.flops > y.flops; });
     const hipStream_t s0 = s;
     const int nst = profile ? 1 : P->nstream;
     double load[jk_plan::MAXSTREAM] = {};
@@ -1175,98 +1322,17 @@ int execute_impl(jk_plan *P, const double *D, int32_t nset, int32_t flags, int32
         HIPCHK(hipEventRecord(P->fork_ev, s0));
         for (int k = 1; k < nst; ++k) HIPCHK(hipStreamWaitEvent(P->streams[k], P->fork_ev, 0));
     }
-    for (size_t ci = 0; ci < P->cls.size(); ++ci) {
-        const ClassTask &c = P->cls[ci];
-        const ClassEntry &e = g_classes[class_id(c.li, c.lj, c.lk, c.ll)];
+    for (const Launch &l : launches) {
         if (nst > 1) {
             int k = 0;
             for (int t = 1; t < nst; ++t)
                 if (load[t] < load[k]) k = t;
-            load[k] += c.flops;
+            load[k] += l.flops;
             s = k == 0 ? s0 : P->streams[k];
         }
-        a.ket_list = c.d_ket;
-        a.same = c.same;
-        a.npb = c.npb;
-        a.nq = (int32_t)c.nq;
-        // mixed: a single-precision pass over the quartets below the
-        // threshold, then a double-precision pass over the rest; both walk
-        // the class's tiles and row tasks
-        const bool msplit = precision == JK_MIXED && c.split;  // (else the class runs in FP64)
-        const int npass = msplit ? 2 : 1;
-        for (int pass = 0; pass < npass; ++pass) {
-            const int pr = msplit ? (pass == 0 ? 1 : 0) : (precision == JK_FP32 ? 1 : 0);
-            a.sel = msplit ? (pass == 0 ? SEL_LO : SEL_HI) : SEL_ALL;
-            a.dstage = 0;
-            const int f = c.fam[pr];
-            // tiles (the short rest) of family 3 classes run in the fallback family
-            const int ft = f == 3 ? tile_fallback(c.li, c.lj, c.lk, c.ll) : f;
-            const int slot = (int)(2 * ci + pr) * 4;  // + kind
-            const int ncols = c.ncolK + (c.seg_same ? 0 : c.ncolL);
-            // the double-precision pass of the mixed split runs as tiles: its
-            // quartets are the first few kets of each bra (largest Schwarz
-            // factors), a fraction of one row-mode pass per bra, and tiles
-            // past them end at their first ket
-            // (and every class in the fixed-order mode: the row kernels add
-            // into their LDS rows from several waves, in no fixed order)
-            const bool tiles_only = a.sel == SEL_HI || det;
-            const bool longrows = !tiles_only && c.row_ok[pr] && c.nrow > 0 && e.row[f - 1][pr] &&
-                                  row_lds_bytes(e, f, pr, c.li, c.lj, nset, ncols, 4, c.npb) <= (size_t)ROW_LDS_MAX && !P->no_row;
-            const bool shortrows = !tiles_only && c.row_short[pr] && c.nsrow > 0 && e.srow[f - 1][pr] &&
-                                   (longrows || c.nrow == 0) &&
-                                   row_lds_bytes(e, f, pr, c.li, c.lj, nset, ncols, 1, c.npb) <= (size_t)ROW_LDS_MAX && !P->no_row;
-            if (longrows || shortrows) {
-                a.bra_list = c.d_bra;
-                a.bra_cnt = c.d_cnt;
-                a.tshK = c.d_tshK;
-                a.tshL = c.d_tshL;
-                a.ncolK = c.ncolK;
-                a.ncolL = c.ncolL;
-                a.seg_same = c.seg_same;
-            }
-            if (longrows) {
-                // long bras: 256-lane workgroups over chunks of their kets;
-                // family 1 stages the bra's D rows in LDS where the
-                // workgroup's LDS stays within DSTAGE_LDS_MAX
-                a.row_pos = c.d_rowc[f - 1];
-                a.nrow = c.nrowc[f - 1];
-                a.dstage = f == 1 && k1_dstage_class(c.li, c.lj) && !P->no_dstage &&
-                           row_lds_bytes(e, f, pr, c.li, c.lj, nset, ncols, 4, c.npb) +
-                                   sizeof(double) * (size_t)nset * (ncart(c.li) + ncart(c.lj)) * ncols <=
-                               (size_t)DSTAGE_LDS_MAX;
-                set_count(slot + 1, c.nq_row);
-                if ((rc = mark(slot + 1))) return rc;
-                HIPCHK(e.row[f - 1][pr](a, s));
-            }
-            if (shortrows) {
-                // short bras: one 64-lane workgroup each
-                a.dstage = 0;
-                a.row_pos = c.d_srowt;
-                a.nrow = c.nsrow;
-                set_count(slot + 3, c.nq - c.nq_row);
-                if ((rc = mark(slot + 3))) return rc;
-                HIPCHK(e.srow[f - 1][pr](a, s));
-                a.ntiles = 0;
-            } else if (longrows) {
-                // the short rest as tiles
-                a.bra_list = c.d_sbra;
-                a.bra_cnt = c.d_scnt;
-                a.nbra = c.nsbra;
-                a.tile_off = c.d_stile[ft - 1];
-                a.ntiles = c.nstiles[ft - 1];
-            } else {
-                a.bra_list = c.d_bra;
-                a.bra_cnt = c.d_cnt;
-                a.nbra = c.nbra;
-                a.tile_off = c.d_tile[ft - 1];
-                a.ntiles = c.ntiles[ft - 1];
-            }
-            if (a.ntiles > 0) {
-                set_count(slot, longrows ? c.nq - c.nq_row : c.nq);
-                if ((rc = mark(slot))) return rc;
-                HIPCHK(e.tiles[ft - 1][pr](a, s));
-            }
-        }
+        a.sel = l.sel;
+        if ((rc = mark())) return rc;
+        HIPCHK(l.fn(a, P->d_cls, l.g, l.lds, s));
     }
     s = s0;
     for (int k = 1; k < nst; ++k) {
@@ -1274,16 +1340,17 @@ int execute_impl(jk_plan *P, const double *D, int32_t nset, int32_t flags, int32
         HIPCHK(hipStreamWaitEvent(s0, P->join_ev[k], 0));
     }
     if (profile) {
-        if ((rc = mark(-1))) return rc;
+        if ((rc = mark())) return rc;
         HIPCHK(hipEventSynchronize(P->events[nev - 1]));
         std::vector<int64_t> cnt;
         if ((rc = launch_counts(P, &cnt))) return rc;
-        for (size_t k = 0; k < slots.size(); ++k) {
+        for (size_t k = 0; k < launches.size(); ++k) {
             float ms = 0.f;
             HIPCHK(hipEventElapsedTime(&ms, P->events[k], P->events[k + 1]));
-            jk_class_timing &t = P->timing[slots[k]];
-            const ClassTask &c = P->cls[slots[k] / 8];
-            const int64_t nq = cnt[slots[k]];
+            const int slot = launches[k].slot;
+            jk_class_timing &t = P->timing[slot];
+            const ClassTask &c = P->cls[slot / 8];
+            const int64_t nq = cnt[slot];
             t.ms += ms;
             t.launches += 1;
             t.nquartets += nq;
@@ -1299,13 +1366,12 @@ int execute_impl(jk_plan *P, const double *D, int32_t nset, int32_t flags, int32
         hipLaunchKernelGGL(k_det_collapse, dim3(grid_for(nm, 256)), dim3(256), 0, s, Kc, sc.detL, nm);
         hipLaunchKernelGGL(k_det_collapse, dim3(grid_for(nj, 256)), dim3(256), 0, s, jpb, sc.detL, nj);
     }
-    if (do_j) {
-        const int64_t nt = (int64_t)nset * npair * 64;
-        hipLaunchKernelGGL(k_jp_scatter, dim3(grid_for(nt, 256)), dim3(256), 0, s, P->d_pairs, P->maps.l, jpb, P->njp,
-                           Jc, (int64_t)m, P->naoc, npair, nt);
-    }
+    const int64_t nt = do_j ? (int64_t)nset * npair * 64 : 0;
+    const int nbs = nt ? grid_for(nt, 256) : 0, nbk = do_k ? grid_for(mo, 256) : 0;
+    if (nbs + nbk > 0)
+        hipLaunchKernelGGL(k_scatter_finalize, dim3(nbs + nbk), dim3(256), 0, s, P->d_pairs, jpb, P->njp, Jc, npair, nt, nbs,
+                           P->maps, Kc, K, P->nao, P->naoc, nset, P->sph, acc);
     if (do_j) hipLaunchKernelGGL(k_finalize, dim3(grid_for(mo, 256)), dim3(256), 0, s, P->maps, Jc, J, P->nao, P->naoc, nset, P->sph, acc);
-    if (do_k) hipLaunchKernelGGL(k_finalize, dim3(grid_for(mo, 256)), dim3(256), 0, s, P->maps, Kc, K, P->nao, P->naoc, nset, P->sph, acc);
     HIPCHK(hipGetLastError());
     return JK_OK;
 }
@@ -1334,7 +1400,7 @@ extern "C" int jk_plan_profile(jk_plan *P, int32_t enable) {
         for (int k = 0; k < 2; ++k)
             for (int kind = 0; kind < 4; ++kind) {
                 const ClassTask &c = P->cls[ci];
-                jk_class_timing &t = P->timing[(2 * ci + k) * 4 + kind];
+                jk_class_timing &t = P->timing[work_slot(ci, k, kind)];
                 t.li = c.li; t.lj = c.lj; t.lk = c.lk; t.ll = c.ll;
                 t.npb = c.npb; t.npk = c.npk;
                 t.precision = (k && kind != 2) ? JK_FP32 : JK_FP64;

@@ -314,18 +314,17 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                 if (c.nq <= 0) continue;
                 BatchDesc d{};
                 JkArgs &a = d.a;
+                ClsArgs &k = d.c;
                 a.pairs = P->d_pairs;
                 a.pp = P->d_pp;
-                a.bra_list = c.d_bra;
-                a.bra_cnt = c.d_cnt;
-                a.nbra = c.nbra;
+                k.bra_list = c.d_bra;
+                k.bra_cnt = c.d_cnt;
+                k.nbra = c.nbra;
                 if (kind == 0) {  // (f <= 2 here)
-                    a.tile_off = c.d_tile[f - 1];
-                    a.ntiles = c.ntiles[f - 1];
+                    k.tile_off = c.d_tile[f - 1];
                 }
-                a.ket_list = c.d_ket;
-                a.same = c.same;
-                a.npb = c.npb;
+                k.ket_list = c.d_ket;
+                k.npb = c.npb;
                         a.nq = (int32_t)c.nq;
                 a.tpos = P->d_tpos;
                 a.aoc = P->maps.aoc;
@@ -344,7 +343,7 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                 a.sel = sel;
                 a.mix_thr = mix_threshold;
                 a.tab = P->tab;
-                d.pad[1] = a.ntiles;  // work units (tiles or row tasks)
+                d.pad[1] = kind == 0 ? c.ntiles[f - 1] : 0;  // work units (tiles or row tasks)
                 if (kind == 1) {
                     // every bra of the class: long bras in chunks, short ones whole
                     const size_t first = alltasks.size();
@@ -352,12 +351,11 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                     alltasks.insert(alltasks.end(), c.h_srowt.begin(), c.h_srowt.end());
                     d.pad[1] = (int32_t)((alltasks.size() - first) / 3);
                     d.pad[2] = (int32_t)first;  // offset into the task buffer (host only)
-                    a.nrow = d.pad[1];
-                    a.tshK = c.d_tshK;
-                    a.tshL = c.d_tshL;
-                    a.ncolK = c.ncolK;
-                    a.ncolL = c.ncolL;
-                    a.seg_same = c.seg_same;
+                    k.tshK = c.d_tshK;
+                    k.tshL = c.d_tshL;
+                    k.ncolK = c.ncolK;
+                    k.ncolL = c.ncolL;
+                    k.seg_same = c.seg_same;
                     if (alltasks.size() > (size_t)INT32_MAX) return fail(JK_EINVAL, "too many row tasks");
                 }
                 if (!(kind == 1 || ce.batch[f - 1][pr]))
@@ -407,7 +405,7 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
         const Group &g = b->groups[gi];
         for (int k = 0; k < g.count; ++k) {
             BatchDesc &d = b->hdesc[g.first + k];
-            if (g.kind == 1) d.a.row_pos = b->d_tasks + d.pad[2];
+            if (g.kind == 1) d.c.row_pos = b->d_tasks + d.pad[2];
         }
     }
     // persistent form (JK_BATCH_PERSIST=1; off by default: measured slower

@@ -1,5 +1,6 @@
 // jk_common.h -- data layouts shared by the host planner and the kernels.
 #pragma once
+#include <stddef.h>
 #include <stdint.h>
 
 #ifdef __HIPCC__
@@ -73,6 +74,18 @@ JK_HD constexpr int k3_qw(int li) { return 64 / ncart(li); }
 // Family-1 row kernels that can stage the bra's D rows in LDS: the small
 // bras, whose rows fit the staging budget on molecules of interest.
 JK_HD constexpr bool k1_dstage_class(int li, int lj) { return ncart(li) + ncart(lj) <= 7; }
+// LDS bytes of a family-1 row task: the bra's npb primitive pair records,
+// nset copies of its K rows over ncols columns and of its J_IJ block, and
+// with dstage of its D rows.
+JK_HD constexpr size_t k1_row_lds(int li, int lj, int nset, int ncols, int npb, bool dstage) {
+    return 80 * (size_t)npb + 8 * (size_t)nset * ((size_t)(ncart(li) + ncart(lj)) * ncols * (dstage ? 2 : 1) + ncart(li) * ncart(lj));
+}
+// The 256-lane family-1 row kernels stage the D rows only while the
+// workgroup's LDS stays within this (so the staging does not cost occupancy).
+constexpr int DSTAGE_LDS_MAX = 40 * 1024;
+JK_HD constexpr bool k1_dstage(int li, int lj, int nset, int ncols, int npb) {
+    return k1_dstage_class(li, lj) && k1_row_lds(li, lj, nset, ncols, npb, true) <= (size_t)DSTAGE_LDS_MAX;
+}
 JK_HD constexpr int tile_fallback(int li, int lj, int lk, int ll) { return has_family2(li, lj, lk, ll) ? 2 : 1; }
 // Family 2: lanes per quartet = ncart(li) * ncart(lk) (slot = (a, c)).
 JK_HD constexpr int k2_slots(int li, int lj, int lk, int ll) { return ncart(li) * ncart(lk); }
@@ -115,32 +128,52 @@ struct Tables {
     const double *mom;     // [e^-T, F_3..F_9] on the T grid (two-root rule)
 };
 
-struct JkArgs {
-    const PairRec *pairs;
-    const PrimPair *pp;
-    // JK mode: tiles over (bra list position, ket chunk)
-    const int32_t *bra_list, *ket_list, *bra_cnt, *tile_off;
-    int32_t nbra, ntiles, same;
-    int32_t npb;  // most primitive pairs of a bra (LDS of the row kernels)
-    // EXPORT mode: explicit quartets
-    const int32_t *q_bra, *q_ket;
-    int32_t nq;
-    double *out;
-    // quartets this launch evaluated (after the selection and the density
-    // screening): NSEL_SLOTS counters NSEL_STRIDE apart, picked by workgroup,
-    // so that the waves of a launch do not all add to one address; NULL when
-    // the host knows the count (every quartet selected, no density screening)
-    unsigned long long *nsel;
+// One contraction class (bra pair type, ket pair type) of one kind of work
+// (tiles, row tasks): what its kernel needs beside the arguments that all
+// classes of a build share.  Held in device memory for the plan's lifetime,
+// so that one launch can cover the classes of an angular class.
+struct ClsArgs {
+    const int32_t *bra_list, *bra_cnt, *ket_list;
+    // tiles: first tile of each bra
+    const int32_t *tile_off;
     // row mode: tasks (list position, ket begin, ket end); column segments of the ket
     // shell types (shells of each type in order; tpos = index of a shell
     // within its type); segment L aliases segment K when the types match
     const int32_t *row_pos;
-    int32_t nrow;
-    const int32_t *tpos, *tshK, *tshL, *aoc;
+    const int32_t *tshK, *tshL;
+    int32_t nbra;
+    int32_t npb;  // most primitive pairs of a bra (LDS of the row kernels)
     int32_t ncolK, ncolL, seg_same;
-    // family-1 row mode: the bra's rows of D over the same compressed
-    // columns are staged in LDS once per task (1), so the exchange digestion
-    // reads them there instead of four scattered global loads per element
+    int32_t ctr;  // its evaluated-quartet counters: slot of JkArgs::nsel
+};
+
+// The work of one launch: units (tiles or row tasks) base[k] .. base[k+1] - 1
+// belong to class cls[desc[k]].  Passed by value.
+constexpr int GROUP_MAX = 64;
+struct ClsGroup {
+    int32_t n;
+    int32_t desc[GROUP_MAX];
+    int32_t base[GROUP_MAX + 1];
+};
+
+struct JkArgs {
+    const PairRec *pairs;
+    const PrimPair *pp;
+    // EXPORT mode: explicit quartets
+    const int32_t *q_bra, *q_ket;
+    int32_t nq;
+    double *out;
+    // quartets a launch evaluated (after the selection and the density
+    // screening): per class NSEL_SLOTS counters NSEL_STRIDE apart, picked by
+    // workgroup, so that the waves of a launch do not all add to one address;
+    // NULL when the host knows the count (every quartet selected, no density
+    // screening)
+    unsigned long long *nsel;
+    const int32_t *tpos, *aoc;
+    // family-1 row mode: the bra's rows of D over the K rows' columns are
+    // staged in LDS once per task where they fit (k1_dstage), so the exchange
+    // digestion reads them there instead of four scattered global loads per
+    // element; 0: never
     int32_t dstage;
     // fixed-order accumulation (JK_DETERMINISTIC): J, K and jp each hold
     // three 64-bit integer limbs per element, det elements apart (0: FP64

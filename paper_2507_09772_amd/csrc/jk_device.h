@@ -559,11 +559,32 @@ __device__ __forceinline__ bool prefix_selectable(const JkArgs &a, double qb, do
 // quartets the wave evaluates; a wave with none skips the work as a whole.
 __device__ __forceinline__ int count_selected(bool mine) { return (int)__popcll(__ballot(mine)); }
 
-// Adds a wave's evaluated quartets to the launch's counters (one atomic from
+// Adds a wave's evaluated quartets to its class's counters (one atomic from
 // one lane; the slot follows the workgroup).
-__device__ __forceinline__ void add_count(const JkArgs &a, int n) {
+__device__ __forceinline__ void add_count(const JkArgs &a, const ClsArgs &c, int n) {
     if (a.nsel && n > 0 && lane_index() == 0)
-        atomicAdd(&a.nsel[(blockIdx.x % NSEL_SLOTS) * NSEL_STRIDE], (unsigned long long)n);
+        atomicAdd(&a.nsel[((size_t)c.ctr * NSEL_SLOTS + blockIdx.x % NSEL_SLOTS) * NSEL_STRIDE], (unsigned long long)n);
+}
+
+// The class of a launch's unit g (uniform in the wave); g becomes the unit
+// within that class.  One launch covers the classes of an angular class:
+// their tiles and row tasks fill the device together, where one launch each
+// left it with few workgroups and a tail per class (launches per FP64 build
+// and time: 3 waters basis A 231 -> about 30, 2.56 -> 0.73 ms; 13 waters 314,
+// 4.1 -> 1.75 ms; 64 waters 380, 50.9 -> 47.5 ms; 32 waters basis B 1182,
+// 374 -> 366 ms).  The class block is
+// written before the launch and only read by kernels, so it is read through
+// the constant address space (scalar loads, a field where it is used).
+__device__ __forceinline__ const ClsArgs &group_class(const ClsArgs *cls, const ClsGroup &grp, int &g) {
+    int lo = 0, hi = grp.n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (grp.base[mid] <= g) lo = mid;
+        else hi = mid - 1;
+    }
+    g -= grp.base[lo];
+    using CCls = const __attribute__((address_space(4))) ClsArgs;
+    return *(const ClsArgs *)&((CCls *)cls)[grp.desc[lo]];
 }
 
 __device__ __forceinline__ double pair_weight(int bra, int ket, const PairRec &B, const PairRec &K) {
@@ -953,34 +974,35 @@ __device__ __forceinline__ void k1_body(const JkArgs &a, int bra, int ket, bool 
 
 // One tile (64 kets of one bra) for one wave.
 template <int LI, int LJ, int LK, int LL, typename R>
-__device__ __forceinline__ void k1_tile(const JkArgs &a, int wave) {
+__device__ __forceinline__ void k1_tile(const JkArgs &a, const ClsArgs &c, int wave) {
     const int lane = lane_index();
     {
-        const int i = tile_bra(a.tile_off, a.nbra, wave);
-        const int j0 = (wave - a.tile_off[i]) * 64, j = j0 + lane;
-        const int cnt = a.bra_cnt[i];
+        const int i = tile_bra(c.tile_off, c.nbra, wave);
+        const int j0 = (wave - c.tile_off[i]) * 64, j = j0 + lane;
+        const int cnt = c.bra_cnt[i];
         bool valid = j < cnt;
-        const int bra = a.bra_list[i];
+        const int bra = c.bra_list[i];
         const PairRec &B = a.pairs[bra];
-        if (!prefix_selectable(a, B.q, a.pairs[a.ket_list[j0]].q)) return;
-        const int ket = a.ket_list[valid ? j : cnt - 1];
+        if (!prefix_selectable(a, B.q, a.pairs[c.ket_list[j0]].q)) return;
+        const int ket = c.ket_list[valid ? j : cnt - 1];
         const PairRec &Kt = a.pairs[ket];
         const double wq = pair_weight(bra, ket, B, Kt);
         screen_quartet(a, B, Kt, valid);
         const int n = count_selected(valid);
         if (n == 0) return;
-        add_count(a, n);
+        add_count(a, c, n);
         k1_body<LI, LJ, LK, LL, R, MODE_JK>(a, bra, ket, valid, wq, 0);
     }
 }
 
 // Tiles: one wave per tile of 64 kets of one bra.
 template <int LI, int LJ, int LK, int LL, typename R, int MODE>
-__global__ void __launch_bounds__(256) jk_k1(const JkArgs a) {
+__global__ void __launch_bounds__(256) jk_k1(const JkArgs a, const ClsArgs *__restrict__ cls, const ClsGroup grp) {
     if constexpr (MODE == MODE_JK) {
-        const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-        if (wave >= a.ntiles) return;
-        k1_tile<LI, LJ, LK, LL, R>(a, wave);
+        int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+        if (wave >= grp.base[grp.n]) return;
+        const ClsArgs &c = group_class(cls, grp, wave);
+        k1_tile<LI, LJ, LK, LL, R>(a, c, wave);
     } else {
         const int g = blockIdx.x * 256 + threadIdx.x;
         const bool valid = g < a.nq;
@@ -991,18 +1013,19 @@ __global__ void __launch_bounds__(256) jk_k1(const JkArgs a) {
 
 struct BatchDesc {
     JkArgs a;
+    ClsArgs c;
     int32_t tile_base;
     int32_t pad[3];
 };
 
-// The argument block of descriptor m.  The descriptors are written before
+// The argument blocks of descriptor m.  The descriptors are written before
 // the launch and only read by the kernels, so they are read through the
 // constant address space: the compiler may then load a field where it is
 // used (and load it again later) instead of holding the whole block in
 // registers, which made the batched family-1 row kernels spill.
-__device__ __forceinline__ const JkArgs &desc_args(const BatchDesc *descs, int m) {
+__device__ __forceinline__ const BatchDesc &desc_args(const BatchDesc *descs, int m) {
     using CDesc = const __attribute__((address_space(4))) BatchDesc;
-    return *(const JkArgs *)&((CDesc *)descs)[m].a;
+    return *(const BatchDesc *)&((CDesc *)descs)[m];
 }
 
 __device__ __forceinline__ int batch_desc(const BatchDesc *__restrict__ d, int n, int g) {
@@ -1024,28 +1047,33 @@ __device__ __forceinline__ int batch_desc(const BatchDesc *__restrict__ d, int n
 // NT = 256 for long bras, 64 for short ones;
 // BATCH: the task indexes the row tasks of many descriptors (molecules).
 template <int LI, int LJ, int LK, int LL, typename R, int NT>
-__device__ __forceinline__ void k1_row_task(const JkArgs &a, int task) {
+__device__ __forceinline__ void k1_row_task(const JkArgs &a, const ClsArgs &c, int task) {
     using C = Cls<LI, LJ, LK, LL>;
     constexpr int NI = C::NI, NJ = C::NJ, NK = C::NK, NL = C::NL, NAB = C::NAB, NCD = C::NCD;
     extern __shared__ double rowmem[];
+    // Blocks of more than 110 elements: lanes without a quartet go through the
+    // digestion with weight zero instead of being masked.  Masked, the values
+    // of the block that are spilled inside were wrong for the next density
+    // in one such kernel ((fp|ds) in single precision, 256 lanes).
+    constexpr bool BIG = C::NC > 110;
     const int tid = threadIdx.x, lane = lane_index();
-    const int i = a.row_pos[3 * task];
-    const int jbeg = a.row_pos[3 * task + 1], cnt = a.row_pos[3 * task + 2];
-    const int bra = a.bra_list[i];
-    const int ncols = a.ncolK + (a.seg_same ? 0 : a.ncolL);
-    const int segL = a.seg_same ? 0 : a.ncolK;
+    const int i = c.row_pos[3 * task];
+    const int jbeg = c.row_pos[3 * task + 1], cnt = c.row_pos[3 * task + 2];
+    const int bra = c.bra_list[i];
+    const int ncols = c.ncolK + (c.seg_same ? 0 : c.ncolL);
+    const int segL = c.seg_same ? 0 : c.ncolK;
     const int per_set = (NI + NJ) * ncols + NAB;
     const PairRec B = a.pairs[bra];
     // a task none of whose quartets can be selected ends here (uniform in the workgroup)
-    if (!prefix_selectable(a, B.q, a.pairs[a.ket_list[jbeg]].q)) return;
+    if (!prefix_selectable(a, B.q, a.pairs[c.ket_list[jbeg]].q)) return;
     // the bra's primitive pair records, then the rows
     PrimPair *sbra = reinterpret_cast<PrimPair *>(rowmem);
-    double *rows = rowmem + (size_t)a.npb * (sizeof(PrimPair) / sizeof(double));
-    // staged D rows of the bra (a.dstage): [nset][NI + NJ][ncols], column c
-    // holding the AO of the K row's column c
-    // (compiled in for the small bras only, where it can fit the LDS budget)
-    constexpr bool DST = k1_dstage_class(LI, LJ);
-    const bool dstage = DST && a.dstage;
+    double *rows = rowmem + (size_t)c.npb * (sizeof(PrimPair) / sizeof(double));
+    // staged D rows of the bra: [nset][NI + NJ][ncols], column c holding the
+    // AO of the K row's column c
+    // (compiled in for the small bras of 256-lane workgroups only, where it
+    // can fit the LDS budget)
+    const bool dstage = NT == 256 && a.dstage && k1_dstage(LI, LJ, a.nset, ncols, c.npb);
     const int dper = (NI + NJ) * ncols;
     double *drows = rows + (size_t)per_set * a.nset;
     const int n = a.nao;
@@ -1054,20 +1082,20 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, int task) {
     if (dstage) {
         for (int t = tid; t < dper * a.nset; t += NT) {
             const int s = t / dper, e = t - s * dper;
-            const int r = e / ncols, c = e - r * ncols;
+            const int r = e / ncols, cc = e - r * ncols;
             const int row = r < NI ? B.aoi + r : B.aoj + (r - NI);
-            const int col = c < a.ncolK ? a.aoc[a.tshK[c / NK]] + c % NK
-                                        : a.aoc[a.tshL[(c - a.ncolK) / NL]] + (c - a.ncolK) % NL;
+            const int col = cc < c.ncolK ? a.aoc[c.tshK[cc / NK]] + cc % NK
+                                         : a.aoc[c.tshL[(cc - c.ncolK) / NL]] + (cc - c.ncolK) % NL;
             drows[t] = a.D[s * a.mstride + (int64_t)row * n + col];
         }
     }
     __syncthreads();
     int evaluated = 0;  // quartets this wave evaluated (wave-uniform)
     for (int j0 = jbeg; j0 < cnt; j0 += NT) {
-        if (!prefix_selectable(a, B.q, a.pairs[a.ket_list[j0]].q)) break;  // uniform in the workgroup
+        if (!prefix_selectable(a, B.q, a.pairs[c.ket_list[j0]].q)) break;  // uniform in the workgroup
         const int j = j0 + tid;
         bool valid = j < cnt;
-        const int ket = a.ket_list[valid ? j : cnt - 1];
+        const int ket = c.ket_list[valid ? j : cnt - 1];
         const PairRec Kt = a.pairs[ket];
         const double wq = pair_weight(bra, ket, B, Kt);
         screen_quartet(a, B, Kt, valid);
@@ -1108,18 +1136,19 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, int task) {
 #pragma unroll
                 for (int m = 0; m < NM; ++m)
                     if (lane + 64 * m < NAB) atomicAdd(&jij[lane + 64 * m], mine[m]);
-                if (valid) {
+                if (BIG || valid) {
                     double *jq = a.jp + s * a.jpstride + Kt.jp_off;
 #pragma unroll
                     for (int cd2 = 0; cd2 < NCD; ++cd2) {
                         double s2 = 0.0;
 #pragma unroll
                         for (int ab2 = 0; ab2 < NAB; ++ab2) s2 += (double)V[ab2 * NCD + cd2] * dij[ab2];
-                        atomic_add_f64(&jq[(int64_t)cd2 * Kt.pp_stride], w2 * s2);
+                        if (!BIG || valid) atomic_add_f64(&jq[(int64_t)cd2 * Kt.pp_stride], w2 * s2);
                     }
                 }
             }
-            if (a.do_k && valid) {
+            if (a.do_k && (BIG || valid)) {
+                const double wk = valid ? wq : 0.0;
                 double djl[NJ * NL], djk[NJ * NK], dil[NI * NL], dik[NI * NK];
                 if (dstage) {
                     const double *dr = drows + s * dper;
@@ -1163,7 +1192,7 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, int task) {
 #pragma unroll
                             for (int l = 0; l < NL; ++l)
                                 s2 += (double)V[((i2 * NJ + j2) * NK + k) * NL + l] * djl[j2 * NL + l];
-                        atomicAdd(&rI[i2 * ncols + cK + k], wq * s2);
+                        atomicAdd(&rI[i2 * ncols + cK + k], wk * s2);
                     }
 #pragma unroll
                 for (int i2 = 0; i2 < NI; ++i2)
@@ -1175,7 +1204,7 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, int task) {
 #pragma unroll
                             for (int k = 0; k < NK; ++k)
                                 s2 += (double)V[((i2 * NJ + j2) * NK + k) * NL + l] * djk[j2 * NK + k];
-                        atomicAdd(&rI[i2 * ncols + cL + l], wq * s2);
+                        atomicAdd(&rI[i2 * ncols + cL + l], wk * s2);
                     }
 #pragma unroll
                 for (int j2 = 0; j2 < NJ; ++j2)
@@ -1187,7 +1216,7 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, int task) {
 #pragma unroll
                             for (int l = 0; l < NL; ++l)
                                 s2 += (double)V[((i2 * NJ + j2) * NK + k) * NL + l] * dil[i2 * NL + l];
-                        atomicAdd(&rJ[j2 * ncols + cK + k], wq * s2);
+                        atomicAdd(&rJ[j2 * ncols + cK + k], wk * s2);
                     }
 #pragma unroll
                 for (int j2 = 0; j2 < NJ; ++j2)
@@ -1199,12 +1228,12 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, int task) {
 #pragma unroll
                             for (int k = 0; k < NK; ++k)
                                 s2 += (double)V[((i2 * NJ + j2) * NK + k) * NL + l] * dik[i2 * NK + k];
-                        atomicAdd(&rJ[j2 * ncols + cL + l], wq * s2);
+                        atomicAdd(&rJ[j2 * ncols + cL + l], wk * s2);
                     }
             }
         }
     }
-    add_count(a, evaluated);
+    add_count(a, c, evaluated);
     __syncthreads();
     // flush nonzero entries to the global J', K'
     for (int s = 0; s < a.nset; ++s) {
@@ -1219,11 +1248,11 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, int task) {
                 atomic_add_f64(&Jm[(B.aoi + e / NJ) * n + B.aoj + e % NJ], v);
                 continue;
             }
-            const int r = t / ncols, c = t % ncols;
+            const int r = t / ncols, cc = t % ncols;
             const int row = r < NI ? B.aoi + r : B.aoj + (r - NI);
             int col;
-            if (c < a.ncolK) col = a.aoc[a.tshK[c / NK]] + c % NK;
-            else col = a.aoc[a.tshL[(c - a.ncolK) / NL]] + (c - a.ncolK) % NL;
+            if (cc < c.ncolK) col = a.aoc[c.tshK[cc / NK]] + cc % NK;
+            else col = a.aoc[c.tshL[(cc - c.ncolK) / NL]] + (cc - c.ncolK) % NL;
             atomic_add_f64(&Km[row * n + col], v);
         }
     }
@@ -1237,13 +1266,16 @@ constexpr int k1_row_waves(int li, int lj, int lk, int ll, int rsize) {
 }
 template <int LI, int LJ, int LK, int LL, typename R, int NT, bool BATCH>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(k1_row_waves(LI, LJ, LK, LL, sizeof(R)))))
-jk_k1_row(const JkArgs a, const BatchDesc *__restrict__ descs, int ndesc) {
+jk_k1_row(const JkArgs a, const ClsArgs *__restrict__ cls, const ClsGroup grp, const BatchDesc *__restrict__ descs,
+          int ndesc) {
+    int task = blockIdx.x;
     if constexpr (BATCH) {
-        const int g = blockIdx.x;
-        const int m = __builtin_amdgcn_readfirstlane(batch_desc(descs, ndesc, g));
-        k1_row_task<LI, LJ, LK, LL, R, NT>(desc_args(descs, m), g - descs[m].tile_base);
+        const int m = __builtin_amdgcn_readfirstlane(batch_desc(descs, ndesc, task));
+        const BatchDesc &d = desc_args(descs, m);
+        k1_row_task<LI, LJ, LK, LL, R, NT>(d.a, d.c, task - d.tile_base);
     } else {
-        k1_row_task<LI, LJ, LK, LL, R, NT>(a, blockIdx.x);
+        const ClsArgs &c = group_class(cls, grp, task);
+        k1_row_task<LI, LJ, LK, LL, R, NT>(a, c, task);
     }
 }
 
@@ -1590,27 +1622,27 @@ __device__ __forceinline__ void k2_body(const JkArgs &a, R *tabs, double *dig, i
 // pointers, the compiler kept the large FP64 classes' accumulators in
 // scratch (four times the private memory of the in-place form) and the
 // (ff|ff) kernel returned wrong values.
-#define JK_K2_TILE(a, wave)                                                     \
+#define JK_K2_TILE(a, c, wave)                                                  \
     do {                                                                        \
-        const int i_ = tile_bra((a).tile_off, (a).nbra, (wave));                \
-        const int j0_ = ((wave) - (a).tile_off[i_]) * QW;                       \
+        const int i_ = tile_bra((c).tile_off, (c).nbra, (wave));                \
+        const int j0_ = ((wave) - (c).tile_off[i_]) * QW;                       \
         const int j_ = j0_ + qq;                                                \
-        const int cnt_ = (a).bra_cnt[i_];                                       \
+        const int cnt_ = (c).bra_cnt[i_];                                       \
         bool valid_ = lane_used && j_ < cnt_;                                   \
-        const int bra_ = (a).bra_list[i_];                                      \
-        if (!prefix_selectable((a), (a).pairs[bra_].q, (a).pairs[(a).ket_list[j0_]].q)) break; \
-        const int ket_ = (a).ket_list[j_ < cnt_ ? j_ : cnt_ - 1];               \
+        const int bra_ = (c).bra_list[i_];                                      \
+        if (!prefix_selectable((a), (a).pairs[bra_].q, (a).pairs[(c).ket_list[j0_]].q)) break; \
+        const int ket_ = (c).ket_list[j_ < cnt_ ? j_ : cnt_ - 1];               \
         const PairRec &B_ = (a).pairs[bra_];                                    \
         const PairRec &K_ = (a).pairs[ket_];                                    \
         const double wq_ = pair_weight(bra_, ket_, B_, K_);                     \
         screen_quartet((a), B_, K_, valid_);                                    \
         const int n_ = count_selected(valid_ && sl == 0);                       \
-        add_count((a), n_);                                                     \
+        add_count((a), (c), n_);                                                \
         if (n_ > 0) k2_body<LI, LJ, LK, LL, R, MODE_JK>((a), tabs, dig, bra_, ket_, valid_, wq_, 0); \
     } while (0)
 
 template <int LI, int LJ, int LK, int LL, typename R, int MODE>
-__global__ void __launch_bounds__(64) jk_k2(const JkArgs a) {
+__global__ void __launch_bounds__(64) jk_k2(const JkArgs a, const ClsArgs *__restrict__ cls, const ClsGroup grp) {
     using F = K2Cfg<LI, LJ, LK, LL>;
     constexpr int QW = F::QW, LPQ = F::LPQ;
     __shared__ R tabs[QW * F::TAB];
@@ -1621,7 +1653,9 @@ __global__ void __launch_bounds__(64) jk_k2(const JkArgs a) {
     const bool lane_used = q < QW;
     const int qq = lane_used ? q : 0;
     if constexpr (MODE == MODE_JK) {
-        JK_K2_TILE(a, (int)blockIdx.x);
+        int wave = (int)blockIdx.x;
+        const ClsArgs &c = group_class(cls, grp, wave);
+        JK_K2_TILE(a, c, wave);
     } else {
         const int gq = blockIdx.x * QW + qq;
         const bool valid = lane_used && gq < a.nq;
@@ -1650,7 +1684,8 @@ struct K2RowLds {
 // layer hipcc moved the (ff|ff) FP64 accumulators to scratch and the kernel
 // returned wrong values, as with the tile prologue.)
 template <int LI, int LJ, int LK, int LL, typename R, int NT, bool BATCH>
-__global__ void __launch_bounds__(NT) jk_k2_row(const JkArgs a_in, const BatchDesc *__restrict__ descs, int ndesc) {
+__global__ void __launch_bounds__(NT) jk_k2_row(const JkArgs a_in, const ClsArgs *__restrict__ cls, const ClsGroup grp,
+                                                const BatchDesc *__restrict__ descs, int ndesc) {
     using C = Cls<LI, LJ, LK, LL>;
     using F = K2Cfg<LI, LJ, LK, LL>;
     constexpr int NI = C::NI, NJ = C::NJ, NAB = C::NAB;
@@ -1660,20 +1695,21 @@ __global__ void __launch_bounds__(NT) jk_k2_row(const JkArgs a_in, const BatchDe
     int task = blockIdx.x, m = 0;
     if constexpr (BATCH) {
         m = __builtin_amdgcn_readfirstlane(batch_desc(descs, ndesc, task));
-        task -= descs[m].tile_base;
+        task -= desc_args(descs, m).tile_base;
     }
-    const JkArgs &a = BATCH ? desc_args(descs, m) : a_in;
-    const int ncols = a.ncolK + (a.seg_same ? 0 : a.ncolL);
-    const int segL = a.seg_same ? 0 : a.ncolK;
+    const JkArgs &a = BATCH ? desc_args(descs, m).a : a_in;
+    const ClsArgs &c = BATCH ? desc_args(descs, m).c : group_class(cls, grp, task);
+    const int ncols = c.ncolK + (c.seg_same ? 0 : c.ncolL);
+    const int segL = c.seg_same ? 0 : c.ncolK;
     const int per_set = (NI + NJ) * ncols + NAB;
     double *rows = smem2;
     double *dig = rows + (size_t)per_set * a.nset + (size_t)wave * F::DIGW;
     R *tabs = (R *)(rows + (size_t)per_set * a.nset + NW * F::DIGW) + (size_t)wave * QW * F::TAB;
-    const int i = a.row_pos[3 * task];
-    const int jbeg = a.row_pos[3 * task + 1], cnt = a.row_pos[3 * task + 2];
-    const int bra = a.bra_list[i];
+    const int i = c.row_pos[3 * task];
+    const int jbeg = c.row_pos[3 * task + 1], cnt = c.row_pos[3 * task + 2];
+    const int bra = c.bra_list[i];
     // a task none of whose quartets can be selected ends here (uniform in the workgroup)
-    if (!prefix_selectable(a, a.pairs[bra].q, a.pairs[a.ket_list[jbeg]].q)) return;
+    if (!prefix_selectable(a, a.pairs[bra].q, a.pairs[c.ket_list[jbeg]].q)) return;
     for (int t = tid; t < per_set * a.nset; t += NT) rows[t] = 0.0;
     __syncthreads();
     const int q = QW > 1 ? lane / LPQ : 0;
@@ -1683,10 +1719,10 @@ __global__ void __launch_bounds__(NT) jk_k2_row(const JkArgs a_in, const BatchDe
     const PairRec &B = a.pairs[bra];
     int evaluated = 0;  // quartets this wave evaluated (wave-uniform)
     for (int j0 = jbeg + wave * QW; j0 < cnt; j0 += NW * QW) {
-        if (!prefix_selectable(a, B.q, a.pairs[a.ket_list[j0]].q)) break;  // uniform in the wave
+        if (!prefix_selectable(a, B.q, a.pairs[c.ket_list[j0]].q)) break;  // uniform in the wave
         const int j = j0 + qq;
         bool valid = lane_used && j < cnt;
-        const int ket = a.ket_list[j < cnt ? j : cnt - 1];
+        const int ket = c.ket_list[j < cnt ? j : cnt - 1];
         const PairRec &Kt = a.pairs[ket];
         const double wq = pair_weight(bra, ket, B, Kt);
         screen_quartet(a, B, Kt, valid);
@@ -1696,7 +1732,7 @@ __global__ void __launch_bounds__(NT) jk_k2_row(const JkArgs a_in, const BatchDe
         evaluated += nv;
         k2_body<LI, LJ, LK, LL, R, MODE_JK, true>(a, tabs, dig, bra, ket, valid, wq, 0, rows, ncols, segL);
     }
-    add_count(a, evaluated);
+    add_count(a, c, evaluated);
     __syncthreads();
     const int n = a.nao;
     for (int s = 0; s < a.nset; ++s) {
@@ -1711,11 +1747,11 @@ __global__ void __launch_bounds__(NT) jk_k2_row(const JkArgs a_in, const BatchDe
                 atomic_add_f64(&Jm[(B.aoi + e / NJ) * n + B.aoj + e % NJ], v);
                 continue;
             }
-            const int r = t / ncols, c = t % ncols;
+            const int r = t / ncols, cc = t % ncols;
             const int row = r < NI ? B.aoi + r : B.aoj + (r - NI);
             int col;
-            if (c < a.ncolK) col = a.aoc[a.tshK[c / ncart(LK)]] + c % ncart(LK);
-            else col = a.aoc[a.tshL[(c - a.ncolK) / ncart(LL)]] + (c - a.ncolK) % ncart(LL);
+            if (cc < c.ncolK) col = a.aoc[c.tshK[cc / ncart(LK)]] + cc % ncart(LK);
+            else col = a.aoc[c.tshL[(cc - c.ncolK) / ncart(LL)]] + (cc - c.ncolK) % ncart(LL);
             atomic_add_f64(&Km[row * n + col], v);
         }
     }
@@ -1832,7 +1868,8 @@ __device__ __forceinline__ void hrr_lane(const R *src, R ab, R cd, R (&T)[(LJ + 
 }
 
 template <int LI, int LJ, int LK, int LL, typename R, int NT, bool BATCH>
-__global__ void __launch_bounds__(NT) jk_k3_row(const JkArgs a_in, const BatchDesc *__restrict__ descs, int ndesc) {
+__global__ void __launch_bounds__(NT) jk_k3_row(const JkArgs a_in, const ClsArgs *__restrict__ cls, const ClsGroup grp,
+                                                const BatchDesc *__restrict__ descs, int ndesc) {
     using C = Cls<LI, LJ, LK, LL>;
     using F = K3Cfg<LI, LJ, LK, LL>;
     constexpr int NI = C::NI, NJ = C::NJ, NK = C::NK, NL = C::NL, NR = C::NR, NAB = C::NAB;
@@ -1842,20 +1879,21 @@ __global__ void __launch_bounds__(NT) jk_k3_row(const JkArgs a_in, const BatchDe
     int task = blockIdx.x, m = 0;
     if constexpr (BATCH) {
         m = __builtin_amdgcn_readfirstlane(batch_desc(descs, ndesc, task));
-        task -= descs[m].tile_base;
+        task -= desc_args(descs, m).tile_base;
     }
-    const JkArgs &a = BATCH ? desc_args(descs, m) : a_in;
-    const int ncols = a.ncolK + (a.seg_same ? 0 : a.ncolL);
-    const int segL = a.seg_same ? 0 : a.ncolK;
+    const JkArgs &a = BATCH ? desc_args(descs, m).a : a_in;
+    const ClsArgs &c = BATCH ? desc_args(descs, m).c : group_class(cls, grp, task);
+    const int ncols = c.ncolK + (c.seg_same ? 0 : c.ncolL);
+    const int segL = c.seg_same ? 0 : c.ncolK;
     const int per_set = (NI + NJ) * ncols + NAB;
     double *rows = smem3;
     double *jkl = rows + (size_t)per_set * a.nset + (size_t)wave * F::JW;
     R *gt = (R *)(rows + (size_t)per_set * a.nset + (size_t)NW * F::JW) + (size_t)wave * F::GW;
-    const int i = a.row_pos[3 * task];
-    const int jbeg = a.row_pos[3 * task + 1], cnt = a.row_pos[3 * task + 2];
-    const int bra = a.bra_list[i];
+    const int i = c.row_pos[3 * task];
+    const int jbeg = c.row_pos[3 * task + 1], cnt = c.row_pos[3 * task + 2];
+    const int bra = c.bra_list[i];
     // a task none of whose quartets can be selected ends here (uniform in the workgroup)
-    if (!prefix_selectable(a, a.pairs[bra].q, a.pairs[a.ket_list[jbeg]].q)) return;
+    if (!prefix_selectable(a, a.pairs[bra].q, a.pairs[c.ket_list[jbeg]].q)) return;
     for (int t = tid; t < per_set * a.nset; t += NT) rows[t] = 0.0;
     for (int t = lane; t < F::JW; t += 64) jkl[t] = 0.0;
     __syncthreads();
@@ -1872,10 +1910,10 @@ __global__ void __launch_bounds__(NT) jk_k3_row(const JkArgs a_in, const BatchDe
     const int n = a.nao;
     int evaluated = 0;  // quartets this wave evaluated (wave-uniform)
     for (int j0 = jbeg + wave * QW; j0 < cnt; j0 += NW * QW) {
-        if (!prefix_selectable(a, B.q, a.pairs[a.ket_list[j0]].q)) break;  // uniform in the wave
+        if (!prefix_selectable(a, B.q, a.pairs[c.ket_list[j0]].q)) break;  // uniform in the wave
         const int j = j0 + qq;
         bool valid = lane_used && j < cnt;
-        const int ket = a.ket_list[j < cnt ? j : cnt - 1];
+        const int ket = c.ket_list[j < cnt ? j : cnt - 1];
         const PairRec Kt = a.pairs[ket];
         const double wq = pair_weight(bra, ket, B, Kt);
         screen_quartet(a, B, Kt, valid);
@@ -2029,7 +2067,7 @@ __global__ void __launch_bounds__(NT) jk_k3_row(const JkArgs a_in, const BatchDe
                     jkl[t] = 0.0;
                     const int j2 = j0 + q2;
                     if (j2 < cnt && v != 0.0) {
-                        const PairRec &K2 = a.pairs[a.ket_list[j2]];
+                        const PairRec &K2 = a.pairs[c.ket_list[j2]];
                         atomic_add_f64(&a.jp[s * a.jpstride + K2.jp_off + (int64_t)e * K2.pp_stride], v);
                     }
                 }
@@ -2037,7 +2075,7 @@ __global__ void __launch_bounds__(NT) jk_k3_row(const JkArgs a_in, const BatchDe
             }
         }
     }
-    add_count(a, evaluated);
+    add_count(a, c, evaluated);
     __syncthreads();
     // flush nonzero entries to the global J', K'
     for (int s = 0; s < a.nset; ++s) {
@@ -2052,11 +2090,11 @@ __global__ void __launch_bounds__(NT) jk_k3_row(const JkArgs a_in, const BatchDe
                 atomic_add_f64(&Jm[(B.aoi + e / NJ) * n + B.aoj + e % NJ], v);
                 continue;
             }
-            const int r = t / ncols, c = t % ncols;
+            const int r = t / ncols, cc = t % ncols;
             const int row = r < NI ? B.aoi + r : B.aoj + (r - NI);
             int col;
-            if (c < a.ncolK) col = a.aoc[a.tshK[c / NK]] + c % NK;
-            else col = a.aoc[a.tshL[(c - a.ncolK) / NL]] + (c - a.ncolK) % NL;
+            if (cc < c.ncolK) col = a.aoc[c.tshK[cc / NK]] + cc % NK;
+            else col = a.aoc[c.tshL[(cc - c.ncolK) / NL]] + (cc - c.ncolK) % NL;
             atomic_add_f64(&Km[row * n + col], v);
         }
     }
@@ -2074,7 +2112,8 @@ __global__ void __launch_bounds__(256) jk_k1_batch(const BatchDesc *__restrict__
     const int g = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
     if (g >= total) return;
     const int m = __builtin_amdgcn_readfirstlane(batch_desc(descs, ndesc, g));
-    k1_tile<LI, LJ, LK, LL, R>(desc_args(descs, m), g - descs[m].tile_base);
+    const BatchDesc &d = desc_args(descs, m);
+    k1_tile<LI, LJ, LK, LL, R>(d.a, d.c, g - d.tile_base);
 }
 
 template <int LI, int LJ, int LK, int LL, typename R>
@@ -2090,8 +2129,8 @@ __global__ void __launch_bounds__(64) jk_k2_batch(const BatchDesc *__restrict__ 
     const int qq = lane_used ? q : 0;
     const int g = blockIdx.x;
     const int m = __builtin_amdgcn_readfirstlane(batch_desc(descs, ndesc, g));
-    const JkArgs &a = desc_args(descs, m);
-    JK_K2_TILE(a, g - descs[m].tile_base);
+    const BatchDesc &d = desc_args(descs, m);
+    JK_K2_TILE(d.a, d.c, g - d.tile_base);
 }
 
 }  // namespace jk

@@ -156,6 +156,12 @@ struct ClassTask {
     const int32_t *d_ket = nullptr;
 };
 
+// Kinds of work of one class and precision: its block in jk_plan::d_cls is
+// entry (2 * class + precision) * 4 + kind, and its evaluated quartets go to
+// the counters of the same entry (the short tiles to those of the tiles).
+enum { WORK_TILES = 0, WORK_ROWS = 1, WORK_STILES = 2, WORK_SROWS = 3 };
+inline int work_slot(size_t ci, int pr, int kind) { return (int)(2 * ci + pr) * 4 + kind; }
+
 struct jk_plan {
     int ns = 0, natom = 0, sph = 0, nao = 0, naoc = 0;
     double cutoff = 0.0;
@@ -164,6 +170,8 @@ struct jk_plan {
     std::vector<PairRec> hpairs;
     std::vector<double> Qsh;
     std::vector<ClassTask> cls;
+    std::vector<std::vector<int>> ang;  // classes of each angular class, heaviest first
+    ClsArgs *d_cls = nullptr;           // [class][precision][kind] (work_slot)
     std::vector<void *> allocs;  // everything below is freed with the plan
     ShellDev sh{};
     PairRec *d_pairs = nullptr;

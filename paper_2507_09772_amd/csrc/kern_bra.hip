@@ -10,13 +10,19 @@
 
 namespace jk {
 
-template <int LI, int LJ, int LK, int LL, typename R, int MODE>
-static hipError_t launch_k1(const JkArgs &a, hipStream_t s) {
-    int grid;
-    if constexpr (MODE == MODE_JK) grid = (a.ntiles + 3) / 4;
-    else grid = (a.nq + 255) / 256;
+template <int LI, int LJ, int LK, int LL, typename R>
+static hipError_t launch_k1(const JkArgs &a, const ClsArgs *cls, const ClsGroup &g, size_t, hipStream_t s) {
+    const int grid = (g.base[g.n] + 3) / 4;
     if (grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL((jk_k1<LI, LJ, LK, LL, R, MODE>), dim3(grid), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((jk_k1<LI, LJ, LK, LL, R, MODE_JK>), dim3(grid), dim3(256), 0, s, a, cls, g);
+    return hipGetLastError();
+}
+
+template <int LI, int LJ, int LK, int LL, typename R>
+static hipError_t export_k1(const JkArgs &a, hipStream_t s) {
+    if (a.nq <= 0) return hipSuccess;
+    hipLaunchKernelGGL((jk_k1<LI, LJ, LK, LL, R, MODE_EXPORT>), dim3((a.nq + 255) / 256), dim3(256), 0, s, a,
+                       (const ClsArgs *)nullptr, ClsGroup{});
     return hipGetLastError();
 }
 
@@ -29,54 +35,30 @@ static hipError_t lds_opt_in(K kernel, size_t lds, bool &done) {
     return e;
 }
 
-static size_t k1_row_lds(const JkArgs &a, int li, int lj) {
-    const int ncols = a.ncolK + (a.seg_same ? 0 : a.ncolL);
-    return sizeof(PrimPair) * (size_t)a.npb +
-           sizeof(double) * a.nset * ((size_t)(ncart(li) + ncart(lj)) * ncols + (size_t)ncart(li) * ncart(lj)) +
-           (a.dstage ? sizeof(double) * a.nset * (size_t)(ncart(li) + ncart(lj)) * ncols : 0);
+// Row tasks of a group of classes with one of the row kernels.
+#define JK_LAUNCH_ROW(kernel)                                                                                     \
+    if (g.base[g.n] <= 0) return hipSuccess;                                                                      \
+    if (lds > (size_t)ROW_LDS_MAX) return hipErrorInvalidValue;                                                   \
+    static bool opted_in = false;                                                                                 \
+    const hipError_t e = lds_opt_in(&kernel<LI, LJ, LK, LL, R, NT, false>, lds, opted_in);                        \
+    if (e != hipSuccess) return e;                                                                                \
+    hipLaunchKernelGGL((kernel<LI, LJ, LK, LL, R, NT, false>), dim3(g.base[g.n]), dim3(NT), lds, s, a, cls, g,    \
+                       (const BatchDesc *)nullptr, 0);                                                            \
+    return hipGetLastError();
+
+template <int LI, int LJ, int LK, int LL, typename R, int NT>
+static hipError_t launch_row(const JkArgs &a, const ClsArgs *cls, const ClsGroup &g, size_t lds, hipStream_t s) {
+    JK_LAUNCH_ROW(jk_k1_row)
 }
 
 template <int LI, int LJ, int LK, int LL, typename R, int NT>
-static hipError_t launch_row(const JkArgs &a, hipStream_t s) {
-    if (a.nrow <= 0) return hipSuccess;
-    const size_t lds = k1_row_lds(a, LI, LJ);
-    if (lds > (size_t)ROW_LDS_MAX) return hipErrorInvalidValue;
-    static bool opted_in = false;
-    const hipError_t e = lds_opt_in(&jk_k1_row<LI, LJ, LK, LL, R, NT, false>, lds, opted_in);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((jk_k1_row<LI, LJ, LK, LL, R, NT, false>), dim3(a.nrow), dim3(NT), lds, s, a,
-                       (const BatchDesc *)nullptr, 0);
-    return hipGetLastError();
+static hipError_t launch_row2(const JkArgs &a, const ClsArgs *cls, const ClsGroup &g, size_t lds, hipStream_t s) {
+    JK_LAUNCH_ROW(jk_k2_row)
 }
 
 template <int LI, int LJ, int LK, int LL, typename R, int NT>
-static hipError_t launch_row2(const JkArgs &a, hipStream_t s) {
-    if (a.nrow <= 0) return hipSuccess;
-    using L = K2RowLds<LI, LJ, LK, LL>;
-    const int ncols = a.ncolK + (a.seg_same ? 0 : a.ncolL);
-    const size_t lds = (NT / 64) * L::template fixed<R>() + (size_t)a.nset * L::per_set(ncols);
-    if (lds > (size_t)ROW_LDS_MAX) return hipErrorInvalidValue;
-    static bool opted_in = false;
-    const hipError_t e = lds_opt_in(&jk_k2_row<LI, LJ, LK, LL, R, NT, false>, lds, opted_in);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((jk_k2_row<LI, LJ, LK, LL, R, NT, false>), dim3(a.nrow), dim3(NT), lds, s, a,
-                       (const BatchDesc *)nullptr, 0);
-    return hipGetLastError();
-}
-
-template <int LI, int LJ, int LK, int LL, typename R, int NT>
-static hipError_t launch_row3(const JkArgs &a, hipStream_t s) {
-    if (a.nrow <= 0) return hipSuccess;
-    using F = K3Cfg<LI, LJ, LK, LL>;
-    const int ncols = a.ncolK + (a.seg_same ? 0 : a.ncolL);
-    const size_t lds = (NT / 64) * F::template wave_bytes<R>() + (size_t)a.nset * F::per_set(ncols);
-    if (lds > (size_t)ROW_LDS_MAX) return hipErrorInvalidValue;
-    static bool opted_in = false;
-    const hipError_t e = lds_opt_in(&jk_k3_row<LI, LJ, LK, LL, R, NT, false>, lds, opted_in);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((jk_k3_row<LI, LJ, LK, LL, R, NT, false>), dim3(a.nrow), dim3(NT), lds, s, a,
-                       (const BatchDesc *)nullptr, 0);
-    return hipGetLastError();
+static hipError_t launch_row3(const JkArgs &a, const ClsArgs *cls, const ClsGroup &g, size_t lds, hipStream_t s) {
+    JK_LAUNCH_ROW(jk_k3_row)
 }
 
 template <int LI, int LJ, int LK, int LL, typename R>
@@ -86,7 +68,8 @@ static hipError_t launch_row3_batch(const BatchDesc *d, int ndesc, int total, si
     static bool opted_in = false;
     const hipError_t e = lds_opt_in(&jk_k3_row<LI, LJ, LK, LL, R, 64, true>, lds, opted_in);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((jk_k3_row<LI, LJ, LK, LL, R, 64, true>), dim3(total), dim3(64), lds, s, JkArgs{}, d, ndesc);
+    hipLaunchKernelGGL((jk_k3_row<LI, LJ, LK, LL, R, 64, true>), dim3(total), dim3(64), lds, s, JkArgs{},
+                       (const ClsArgs *)nullptr, ClsGroup{}, d, ndesc);
     return hipGetLastError();
 }
 
@@ -98,7 +81,8 @@ static hipError_t launch_row_batch(const BatchDesc *d, int ndesc, int total, siz
     static bool opted_in = false;
     const hipError_t e = lds_opt_in(&jk_k1_row<LI, LJ, LK, LL, R, 64, true>, lds, opted_in);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((jk_k1_row<LI, LJ, LK, LL, R, 64, true>), dim3(total), dim3(64), lds, s, JkArgs{}, d, ndesc);
+    hipLaunchKernelGGL((jk_k1_row<LI, LJ, LK, LL, R, 64, true>), dim3(total), dim3(64), lds, s, JkArgs{},
+                       (const ClsArgs *)nullptr, ClsGroup{}, d, ndesc);
     return hipGetLastError();
 }
 
@@ -109,18 +93,24 @@ static hipError_t launch_row2_batch(const BatchDesc *d, int ndesc, int total, si
     static bool opted_in = false;
     const hipError_t e = lds_opt_in(&jk_k2_row<LI, LJ, LK, LL, R, 64, true>, lds, opted_in);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((jk_k2_row<LI, LJ, LK, LL, R, 64, true>), dim3(total), dim3(64), lds, s, JkArgs{}, d, ndesc);
+    hipLaunchKernelGGL((jk_k2_row<LI, LJ, LK, LL, R, 64, true>), dim3(total), dim3(64), lds, s, JkArgs{},
+                       (const ClsArgs *)nullptr, ClsGroup{}, d, ndesc);
     return hipGetLastError();
 }
 
-template <int LI, int LJ, int LK, int LL, typename R, int MODE>
-static hipError_t launch_k2(const JkArgs &a, hipStream_t s) {
+template <int LI, int LJ, int LK, int LL, typename R>
+static hipError_t launch_k2(const JkArgs &a, const ClsArgs *cls, const ClsGroup &g, size_t, hipStream_t s) {
+    if (g.base[g.n] <= 0) return hipSuccess;
+    hipLaunchKernelGGL((jk_k2<LI, LJ, LK, LL, R, MODE_JK>), dim3(g.base[g.n]), dim3(64), 0, s, a, cls, g);
+    return hipGetLastError();
+}
+
+template <int LI, int LJ, int LK, int LL, typename R>
+static hipError_t export_k2(const JkArgs &a, hipStream_t s) {
     constexpr int QW = k2_qw(LI, LJ, LK, LL);
-    int grid;
-    if constexpr (MODE == MODE_JK) grid = a.ntiles;
-    else grid = (a.nq + QW - 1) / QW;
-    if (grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL((jk_k2<LI, LJ, LK, LL, R, MODE>), dim3(grid), dim3(64), 0, s, a);
+    if (a.nq <= 0) return hipSuccess;
+    hipLaunchKernelGGL((jk_k2<LI, LJ, LK, LL, R, MODE_EXPORT>), dim3((a.nq + QW - 1) / QW), dim3(64), 0, s, a,
+                       (const ClsArgs *)nullptr, ClsGroup{});
     return hipGetLastError();
 }
 
@@ -150,8 +140,8 @@ static void reg_one() {
     if constexpr (LK >= LL && (LK < LI || (LK == LI && LL <= LJ))) {
         ClassEntry &e = g_classes[class_id(LI, LJ, LK, LL)];
         if constexpr (has_family1(LI, LJ, LK, LL)) {
-            e.tiles[0][0] = &launch_k1<LI, LJ, LK, LL, double, MODE_JK>;
-            e.tiles[0][1] = &launch_k1<LI, LJ, LK, LL, float, MODE_JK>;
+            e.tiles[0][0] = &launch_k1<LI, LJ, LK, LL, double>;
+            e.tiles[0][1] = &launch_k1<LI, LJ, LK, LL, float>;
             e.row[0][0] = &launch_row<LI, LJ, LK, LL, double, 256>;
             e.row[0][1] = &launch_row<LI, LJ, LK, LL, float, 256>;
             if constexpr (FULL) {
@@ -164,8 +154,8 @@ static void reg_one() {
             }
         }
         if constexpr (has_family2(LI, LJ, LK, LL)) {
-            e.tiles[1][0] = &launch_k2<LI, LJ, LK, LL, double, MODE_JK>;
-            e.tiles[1][1] = &launch_k2<LI, LJ, LK, LL, float, MODE_JK>;
+            e.tiles[1][0] = &launch_k2<LI, LJ, LK, LL, double>;
+            e.tiles[1][1] = &launch_k2<LI, LJ, LK, LL, float>;
             e.row[1][0] = &launch_row2<LI, LJ, LK, LL, double, 256>;
             e.row[1][1] = &launch_row2<LI, LJ, LK, LL, float, 256>;
             if constexpr (FULL) {
@@ -194,11 +184,11 @@ static void reg_one() {
             e.row_fixed[2][1] = K3Cfg<LI, LJ, LK, LL>::template wave_bytes<float>();
         }
         if constexpr (default_family(LI, LJ, LK, LL) == 1) {
-            e.ex64 = &launch_k1<LI, LJ, LK, LL, double, MODE_EXPORT>;
-            e.ex32 = &launch_k1<LI, LJ, LK, LL, float, MODE_EXPORT>;
+            e.ex64 = &export_k1<LI, LJ, LK, LL, double>;
+            e.ex32 = &export_k1<LI, LJ, LK, LL, float>;
         } else {
-            e.ex64 = &launch_k2<LI, LJ, LK, LL, double, MODE_EXPORT>;
-            e.ex32 = &launch_k2<LI, LJ, LK, LL, float, MODE_EXPORT>;
+            e.ex64 = &export_k2<LI, LJ, LK, LL, double>;
+            e.ex32 = &export_k2<LI, LJ, LK, LL, float>;
         }
     }
 }

@@ -33,11 +33,12 @@ __global__ void __launch_bounds__(64) jk_k1_persist(const BatchDesc *__restrict_
         const int di = __builtin_amdgcn_readfirstlane(items[2 * it]);
         const int task = __builtin_amdgcn_readfirstlane(items[2 * it + 1]);
         const JkArgs a = descs[di].a;
+        const ClsArgs c = descs[di].c;
         const int cid = __builtin_amdgcn_readfirstlane(descs[di].pad[0]);
         switch (cid) {
 #define JK_PC(A, B, C, D)                                  \
     case class_id(A, B, C, D):                             \
-        k1_row_task<A, B, C, D, R, 64>(a, task);           \
+        k1_row_task<A, B, C, D, R, 64>(a, c, task);         \
         break;
             JK_PERSIST_CLASSES(JK_PC)
 #undef JK_PC
