@@ -415,6 +415,38 @@ static int launch_export(jk_plan *P, int li, int lj, int lk, int ll, int precisi
     return 0;
 }
 
+// Lanes (log2) that share one quartet in family-1 tiles, for bras with cnt
+// kets whose longest ket has npk primitive pairs.  A lane runs its quartet's
+// primitive quartets one after another (0.3 to 0.5 us each), so a class with
+// few quartets left the device idle behind a few long chains ((s6 s6|s6 s6)
+// of one water: 21 x 21 of them).  Lanes are added while each gets a ket
+// primitive pair and the class stays within SPLIT_WAVES waves: beyond that
+// its own quartets fill the device (1 water basis A 500 -> 188 us, 3 waters
+// 0.73 -> 0.29 ms, 13 waters 1.75 -> 1.53 ms per FP64 build; larger molecules
+// unchanged).  Double precision only: in single
+// precision the order of a block's sum shows (1e-7 of the largest elements).
+static const int64_t SPLIT_WAVES = 2048;
+static int tile_split(const std::vector<int32_t> &cnt, int npk) {
+    int split = 0;
+    while (split < 5 && (2 << split) <= npk) {
+        int64_t waves = 0;
+        const int per = 64 >> (split + 1);
+        for (int32_t n : cnt) waves += (n + per - 1) / per;
+        if (waves > SPLIT_WAVES) break;
+        ++split;
+    }
+    return split;
+}
+// First tile of every bra (off), for per quartets a tile; returns the tiles.
+static int64_t tile_offsets(const std::vector<int32_t> &cnt, int per, std::vector<int32_t> *off) {
+    int64_t tiles = 0;
+    for (int32_t n : cnt) {
+        off->push_back((int32_t)tiles);
+        tiles += (n + per - 1) / per;
+    }
+    return tiles;
+}
+
 // The classes' argument blocks on the device, and the classes of each
 // angular class (launched together), longest primitive loops first so that
 // the long workgroups of a launch start early.
@@ -425,7 +457,6 @@ static int place_classes(jk_plan *P) {
     for (size_t ci = 0; ci < P->cls.size(); ++ci) {
         const ClassTask &c = P->cls[ci];
         for (int pr = 0; pr < 2; ++pr) {
-            const int f = c.fam[pr], ft = f == 3 ? tile_fallback(c.li, c.lj, c.lk, c.ll) : f;
             ClsArgs b{};
             b.ket_list = c.d_ket;
             b.npb = c.npb;
@@ -437,11 +468,12 @@ static int place_classes(jk_plan *P) {
             b.bra_list = c.d_bra;
             b.bra_cnt = c.d_cnt;
             b.nbra = c.nbra;
-            b.tile_off = c.d_tile[ft - 1];
+            b.tile_off = c.d_tile[pr];
             b.ctr = work_slot(ci, pr, WORK_TILES);
+            b.split = c.tsplit[pr];
             ca[work_slot(ci, pr, WORK_TILES)] = b;
             b.ctr = work_slot(ci, pr, WORK_ROWS);
-            b.row_pos = c.d_rowc[f - 1];
+            b.row_pos = c.d_rowc[c.fam[pr] - 1];
             ca[work_slot(ci, pr, WORK_ROWS)] = b;
             b.ctr = work_slot(ci, pr, WORK_SROWS);
             b.row_pos = c.d_srowt;
@@ -450,8 +482,9 @@ static int place_classes(jk_plan *P) {
             b.bra_list = c.d_sbra;
             b.bra_cnt = c.d_scnt;
             b.nbra = c.nsbra;
-            b.tile_off = c.d_stile[ft - 1];
+            b.tile_off = c.d_stile[pr];
             b.ctr = work_slot(ci, pr, WORK_TILES);
+            b.split = c.tssplit[pr];
             ca[work_slot(ci, pr, WORK_STILES)] = b;
         }
         int &k = of[class_id(c.li, c.lj, c.lk, c.ll)];
@@ -706,9 +739,8 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
                 c.split = g_split[class_id(c.li, c.lj, c.lk, c.ll)] != 2;
                 c.row_short[pr] = g_row[class_id(c.li, c.lj, c.lk, c.ll)][pr] == 3;
             }
-            std::vector<int32_t> bl, cn, to[2];
+            std::vector<int32_t> bl, cn;
             const auto &kq = sortedq[kt];
-            int64_t tiles[2] = {0, 0};
             int64_t npq_eval = 0;  // primitive quartets evaluated
             for (size_t i = 0; i < sorted[bt].size(); ++i) {
                 const double qb = sortedq[bt][i];
@@ -724,25 +756,38 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
                 if (cnt == 0) continue;
                 bl.push_back(sorted[bt][i]);
                 cn.push_back((int32_t)cnt);
-                for (int f = 0; f < 2; ++f) {
-                    to[f].push_back((int32_t)tiles[f]);
-                    const int qpt = quartets_per_tile(f + 1, c.li, c.lj, c.lk, c.ll);
-                    tiles[f] += (cnt + qpt - 1) / qpt;
-                }
                 c.nq += cnt;
                 npq_eval += (int64_t)npp[sorted[bt][i]] * sortedn[kt][cnt];
             }
             if (c.nq == 0) continue;
-            if (tiles[0] > INT32_MAX || tiles[1] > INT32_MAX || c.nq > INT32_MAX)
+            int npk = 1;  // most primitive pairs of a ket
+            for (int p : sorted[kt]) npk = std::max(npk, npp[p]);
+            // tiles of a bra list, per precision in its tile family
+            auto place_tiles = [&](const std::vector<int32_t> &cnt, int32_t *(&dst)[2], int (&count)[2], int (&split)[2]) -> int {
+                for (int pr = 0; pr < 2; ++pr) {
+                    const int f = c.tile_family(pr);
+                    split[pr] = f == 1 && pr == 0 ? tile_split(cnt, npk) : 0;
+                    if (pr == 1 && c.tile_family(0) == f && split[0] == 0) {
+                        dst[1] = dst[0];
+                        count[1] = count[0];
+                        continue;
+                    }
+                    std::vector<int32_t> off;
+                    const int64_t n = tile_offsets(cnt, quartets_per_tile(f, c.li, c.lj, c.lk, c.ll) >> split[pr], &off);
+                    if (n > INT32_MAX) return fail(JK_EUNSUPPORTED, "class (%d%d|%d%d) has too many quartets", c.li, c.lj, c.lk, c.ll);
+                    count[pr] = (int)n;
+                    const int rc2 = P->put(&dst[pr], off);
+                    if (rc2) return rc2;
+                }
+                return 0;
+            };
+            if (c.nq > INT32_MAX)
                 return fail(JK_EUNSUPPORTED, "class (%d%d|%d%d) has too many quartets", c.li, c.lj, c.lk, c.ll);
             c.nbra = (int)bl.size();
             c.npq = c.nq * c.npb * c.npk;
             c.flops = (double)npq_eval * flops_prim(c.li, c.lj, c.lk, c.ll) + (double)c.nq * flops_digest(c.li, c.lj, c.lk, c.ll);
             if ((rc = P->put(&c.d_bra, bl)) || (rc = P->put(&c.d_cnt, cn))) return rc;
-            for (int f = 0; f < 2; ++f) {
-                c.ntiles[f] = (int)tiles[f];
-                if (avail[f] && (rc = P->put(&c.d_tile[f], to[f]))) return rc;
-            }
+            if ((rc = place_tiles(cn, c.d_tile, c.ntiles, c.tsplit))) return rc;
             c.d_ket = d_sorted[kt];
             // row mode split: bras with a long ket prefix get a workgroup each
             {
@@ -752,8 +797,7 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
                 c.seg_same = tK == tL;
                 c.d_tshK = d_tsh[tK];
                 c.d_tshL = d_tsh[tL];
-                std::vector<int32_t> rows, sb, scn, sto[2];
-                int64_t st[2] = {0, 0};
+                std::vector<int32_t> rows, sb, scn;
                 for (size_t i = 0; i < bl.size(); ++i) {
                     const int minkets = g_minkets[class_id(c.li, c.lj, c.lk, c.ll)] > 0
                                             ? g_minkets[class_id(c.li, c.lj, c.lk, c.ll)] : ROW_MIN_KETS;
@@ -768,11 +812,6 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
                     c.h_srowt.push_back(cn[i]);
                     sb.push_back(bl[i]);
                     scn.push_back(cn[i]);
-                    for (int f = 0; f < 2; ++f) {
-                        sto[f].push_back((int32_t)st[f]);
-                        const int qpt = quartets_per_tile(f + 1, c.li, c.lj, c.lk, c.ll);
-                        st[f] += (cn[i] + qpt - 1) / qpt;
-                    }
                 }
                 c.nrow = (int)rows.size();
                 c.nsbra = (int)sb.size();
@@ -798,10 +837,7 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
                     }
                     if (c.nsbra > 0) {
                         if ((rc = P->put(&c.d_sbra, sb)) || (rc = P->put(&c.d_scnt, scn))) return rc;
-                        for (int f = 0; f < 2; ++f) {
-                            c.nstiles[f] = (int)st[f];
-                            if (avail[f] && (rc = P->put(&c.d_stile[f], sto[f]))) return rc;
-                        }
+                        if ((rc = place_tiles(scn, c.d_stile, c.nstiles, c.tssplit))) return rc;
                     }
                 } else {
                     c.nrow = 0;
@@ -1242,7 +1278,7 @@ int execute_impl(jk_plan *P, const double *D, int32_t nset, int32_t flags, int32
             const int sel = msplit ? (pass == 0 ? SEL_LO : SEL_HI) : SEL_ALL;
             const int f = c0.fam[pr];
             // tiles (the short rest) of family 3 classes run in the fallback family
-            const int ft = f == 3 ? tile_fallback(c0.li, c0.lj, c0.lk, c0.ll) : f;
+            const int ft = c0.tile_family(pr);
             // the double-precision pass of the mixed split runs as tiles: its
             // quartets are the first few kets of each bra (largest Schwarz
             // factors), a fraction of one row-mode pass per bra, and tiles
@@ -1292,8 +1328,8 @@ int execute_impl(jk_plan *P, const double *D, int32_t nset, int32_t flags, int32
                 // short bras: one 64-lane workgroup each, or tiles
                 const int64_t nq = longrows ? c.nq - c.nq_row : c.nq;
                 if (shortrows) add(e.srow[f - 1][pr], ci, WORK_SROWS, c.nsrow, lds1, c.nq - c.nq_row);
-                else if (longrows && c.nstiles[ft - 1] > 0) add(e.tiles[ft - 1][pr], ci, WORK_STILES, c.nstiles[ft - 1], 0, nq);
-                else if (!longrows && c.ntiles[ft - 1] > 0) add(e.tiles[ft - 1][pr], ci, WORK_TILES, c.ntiles[ft - 1], 0, nq);
+                else if (longrows && c.nstiles[pr] > 0) add(e.tiles[ft - 1][pr], ci, WORK_STILES, c.nstiles[pr], 0, nq);
+                else if (!longrows && c.ntiles[pr] > 0) add(e.tiles[ft - 1][pr], ci, WORK_TILES, c.ntiles[pr], 0, nq);
             }
         }
     }
@@ -1405,7 +1441,7 @@ extern "C" int jk_plan_profile(jk_plan *P, int32_t enable) {
                 t.npb = c.npb; t.npk = c.npk;
                 t.precision = (k && kind != 2) ? JK_FP32 : JK_FP64;
                 // tiles of a family-3 class run in its fallback family
-                t.family = kind == 0 && c.fam[k] == 3 ? tile_fallback(c.li, c.lj, c.lk, c.ll) : c.fam[k];
+                t.family = kind == 0 ? c.tile_family(k) : c.fam[k];
                 t.kind = kind;
             }
     return 0;

@@ -310,7 +310,7 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                 const size_t lds1 = row_lds_bytes(ce, f, pr, c.li, c.lj, nset, ncols, 1, c.npb);
                 const int kind = c.row_ok[pr] && ce.batch_row[f - 1][pr] && lds1 <= (size_t)ROW_LDS_MAX ? 1 : 0;
                 // tiles of a family-3 class run in its fallback family
-                if (kind == 0 && f == 3) f = tile_fallback(c.li, c.lj, c.lk, c.ll);
+                if (kind == 0) f = c.tile_family(pr);
                 if (c.nq <= 0) continue;
                 BatchDesc d{};
                 JkArgs &a = d.a;
@@ -321,7 +321,8 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                 k.bra_cnt = c.d_cnt;
                 k.nbra = c.nbra;
                 if (kind == 0) {  // (f <= 2 here)
-                    k.tile_off = c.d_tile[f - 1];
+                    k.tile_off = c.d_tile[pr];
+                    k.split = c.tsplit[pr];
                 }
                 k.ket_list = c.d_ket;
                 k.npb = c.npb;
@@ -343,7 +344,7 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                 a.sel = sel;
                 a.mix_thr = mix_threshold;
                 a.tab = P->tab;
-                d.pad[1] = kind == 0 ? c.ntiles[f - 1] : 0;  // work units (tiles or row tasks)
+                d.pad[1] = kind == 0 ? c.ntiles[pr] : 0;  // work units (tiles or row tasks)
                 if (kind == 1) {
                     // every bra of the class: long bras in chunks, short ones whole
                     const size_t first = alltasks.size();

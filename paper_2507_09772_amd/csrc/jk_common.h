@@ -145,6 +145,7 @@ struct ClsArgs {
     int32_t npb;  // most primitive pairs of a bra (LDS of the row kernels)
     int32_t ncolK, ncolL, seg_same;
     int32_t ctr;  // its evaluated-quartet counters: slot of JkArgs::nsel
+    int32_t split;  // family-1 tiles: 2^split lanes share a quartet's ket primitive pairs
 };
 
 // The work of one launch: units (tiles or row tasks) base[k] .. base[k+1] - 1

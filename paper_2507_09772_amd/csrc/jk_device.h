@@ -748,9 +748,10 @@ __device__ __forceinline__ void k1_roots_acc(const PQuart<R> &g, const R *u, con
 // operators (omega != 0) are compiled in; the Coulomb instance has no
 // trace of them (given the chance, the compiler evaluates the root scaling
 // of the other variant on every primitive quartet).
+// The lane takes the ket primitive pairs ik0, ik0 + step, ...
 template <int LI, int LJ, int LK, int LL, typename R, bool RS, typename PBF>
 __device__ __forceinline__ void k1_compute_op(const JkArgs &a, const PairRec &B, const PairRec &Kt, PBF &&pbat, int npb,
-                                              int npk, R (&V)[ncart4(LI, LJ, LK, LL)]) {
+                                              int npk, int ik0, int step, R (&V)[ncart4(LI, LJ, LK, LL)]) {
     using C = Cls<LI, LJ, LK, LL>;
     constexpr int NR = C::NR;
 #pragma unroll
@@ -778,12 +779,12 @@ __device__ __forceinline__ void k1_compute_op(const JkArgs &a, const PairRec &B,
         // (the one-root classes load each ket record when they reach it:
         // their registers, not the load, bound them)
         constexpr bool PREF = NR > 1;
-        PrimPair pk = ket_prim(0);
+        PrimPair pk = ket_prim(ik0);
         settle(pk);
-        for (int ik = 0;;) {
-            const bool next = more(ik + 1);
+        for (int ik = ik0;;) {
+            const bool next = more(ik + step);
             PrimPair pkn;
-            if (PREF && next) pkn = ket_prim(ik + 1);
+            if (PREF && next) pkn = ket_prim(ik + step);
             PT<R> t = prim_T<R>(pbat(0), pk);
             typename P::Row row;
             P::fetch(t.T, a.tab, row);
@@ -797,7 +798,7 @@ __device__ __forceinline__ void k1_compute_op(const JkArgs &a, const PairRec &B,
                 }
                 k1_roots_acc<LI, LJ, LK, LL, R>(g, u, w, ab, cd, V);
             }
-            ++ik;
+            ik += step;
             if (!next) break;
             if constexpr (PREF) {
                 settle(pkn);
@@ -809,7 +810,7 @@ __device__ __forceinline__ void k1_compute_op(const JkArgs &a, const PairRec &B,
         return;
     }
     const int vb = RS ? variant_begin(a.omega) : 0, ve = RS ? variant_end(a.omega) : 1;
-    for (int ik = 0; more(ik); ++ik) {
+    for (int ik = ik0; more(ik); ik += step) {
         const PrimPair pk = ket_prim(ik);
         for (int ib = 0; ib < npb; ++ib) {
             const PQuart<R> g = prim_quartet<R>(pbat(ib), pk);
@@ -825,13 +826,14 @@ __device__ __forceinline__ void k1_compute_op(const JkArgs &a, const PairRec &B,
 
 template <int LI, int LJ, int LK, int LL, typename R, typename PBF>
 __device__ __forceinline__ void k1_compute(const JkArgs &a, const PairRec &B, const PairRec &Kt, PBF &&pbat, int npb,
-                                           int npk, R (&V)[ncart4(LI, LJ, LK, LL)]) {
-    if (a.omega == 0.0) k1_compute_op<LI, LJ, LK, LL, R, false>(a, B, Kt, pbat, npb, npk, V);
-    else k1_compute_op<LI, LJ, LK, LL, R, true>(a, B, Kt, pbat, npb, npk, V);
+                                           int npk, int ik0, int step, R (&V)[ncart4(LI, LJ, LK, LL)]) {
+    if (a.omega == 0.0) k1_compute_op<LI, LJ, LK, LL, R, false>(a, B, Kt, pbat, npb, npk, ik0, step, V);
+    else k1_compute_op<LI, LJ, LK, LL, R, true>(a, B, Kt, pbat, npb, npk, ik0, step, V);
 }
 
 template <int LI, int LJ, int LK, int LL, typename R, int MODE>
-__device__ __forceinline__ void k1_body(const JkArgs &a, int bra, int ket, bool valid, double wq, int64_t gout) {
+__device__ __forceinline__ void k1_body(const JkArgs &a, int bra, int ket, bool valid, double wq, int64_t gout,
+                                        int split = 0) {
     using C = Cls<LI, LJ, LK, LL>;
     constexpr int NI = C::NI, NJ = C::NJ, NK = C::NK, NL = C::NL, NAB = C::NAB, NCD = C::NCD;
     constexpr bool BRA_UNIFORM = MODE == MODE_JK;
@@ -839,8 +841,17 @@ __device__ __forceinline__ void k1_body(const JkArgs &a, int bra, int ket, bool 
     const PairRec B = a.pairs[bra];
     const PairRec Kt = a.pairs[ket];
     R V[C::NC];
+    // 2^split neighbouring lanes share the quartet's ket primitive pairs
+    const int gl = MODE == MODE_JK ? lane & ((1 << split) - 1) : 0;
     k1_compute<LI, LJ, LK, LL, R>(a, B, Kt, [&](int ib) { return a.pp[B.pp_off + ib * B.pp_stride]; },
-                                  B.npp, Kt.npp, V);
+                                  B.npp, Kt.npp, gl, 1 << split, V);
+    if constexpr (MODE == MODE_JK) {
+        for (int off = 1; off < (1 << split); off <<= 1) {
+#pragma unroll
+            for (int e = 0; e < C::NC; ++e) V[e] += __shfl_xor(V[e], off, 64);
+        }
+        valid = valid && gl == 0;
+    }
     if constexpr (MODE == MODE_EXPORT) {
         if (valid) {
             double *o = a.out + gout * (NAB * NCD);
@@ -972,13 +983,15 @@ __device__ __forceinline__ void k1_body(const JkArgs &a, int bra, int ket, bool 
     }
 }
 
-// One tile (64 kets of one bra) for one wave.
+// One tile (64 kets of one bra, or 64 / 2^split with 2^split lanes each) for
+// one wave.
 template <int LI, int LJ, int LK, int LL, typename R>
 __device__ __forceinline__ void k1_tile(const JkArgs &a, const ClsArgs &c, int wave) {
     const int lane = lane_index();
     {
         const int i = tile_bra(c.tile_off, c.nbra, wave);
-        const int j0 = (wave - c.tile_off[i]) * 64, j = j0 + lane;
+        const int split = c.split;
+        const int j0 = (wave - c.tile_off[i]) * (64 >> split), j = j0 + (lane >> split);
         const int cnt = c.bra_cnt[i];
         bool valid = j < cnt;
         const int bra = c.bra_list[i];
@@ -988,10 +1001,10 @@ __device__ __forceinline__ void k1_tile(const JkArgs &a, const ClsArgs &c, int w
         const PairRec &Kt = a.pairs[ket];
         const double wq = pair_weight(bra, ket, B, Kt);
         screen_quartet(a, B, Kt, valid);
-        const int n = count_selected(valid);
+        const int n = count_selected(valid && (lane & ((1 << split) - 1)) == 0);
         if (n == 0) return;
         add_count(a, c, n);
-        k1_body<LI, LJ, LK, LL, R, MODE_JK>(a, bra, ket, valid, wq, 0);
+        k1_body<LI, LJ, LK, LL, R, MODE_JK>(a, bra, ket, valid, wq, 0, split);
     }
 }
 
@@ -1104,7 +1117,7 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, const ClsArgs &c, i
         if (nv == 0) continue;
         evaluated += nv;
         R V[C::NC];
-        k1_compute<LI, LJ, LK, LL, R>(a, B, Kt, [&](int ib) { return sbra[ib]; }, B.npp, Kt.npp, V);
+        k1_compute<LI, LJ, LK, LL, R>(a, B, Kt, [&](int ib) { return sbra[ib]; }, B.npp, Kt.npp, 0, 1, V);
         const int cK = a.tpos[Kt.ish] * NK, cL = segL + a.tpos[Kt.jsh] * NL;
         for (int s = 0; s < a.nset; ++s) {
             const double *D = a.D + s * a.mstride;

@@ -134,7 +134,7 @@ struct ClassTask {
     int li, lj, lk, ll;
     int bt, kt, same, npb, npk, nbra;
     // row mode: long bras (positions into d_bra / d_cnt) and the short rest
-    int nrow = 0, nsbra = 0, nstiles[2] = {0, 0};
+    int nrow = 0, nsbra = 0, nstiles[2] = {0, 0};  // short tiles per precision
     int64_t nq_row = 0;  // quartets of the long bras
     int nrowc[3] = {0, 0, 0};                    // row tasks per family
     int32_t *d_rowc[3] = {nullptr, nullptr, nullptr};  // (list position, ket begin, ket end) per task
@@ -149,7 +149,10 @@ struct ClassTask {
     bool split = true;   // mixed builds split this class by the bound (else all FP64)
     bool row_ok[2];      // row mode allowed per precision
     bool row_short[2];   // short bras in row mode too (64-lane workgroups)
-    int ntiles[2];       // per family - 1
+    // tiles per precision (in tile_family(pr))
+    int ntiles[2] = {0, 0};
+    int tsplit[2] = {0, 0}, tssplit[2] = {0, 0};  // lanes (log2) per quartet of family-1 tiles, all and short
+    int tile_family(int pr) const { return fam[pr] == 3 ? tile_fallback(li, lj, lk, ll) : fam[pr]; }
     int64_t nq, npq;
     double flops;
     int32_t *d_bra = nullptr, *d_cnt = nullptr, *d_tile[2] = {nullptr, nullptr};

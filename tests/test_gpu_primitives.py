@@ -87,3 +87,31 @@ def test_matrices_of_contracted_shells(env, nprim, signs):
         assert np.abs(J.cpu().numpy() - J0).max() <= tol
         assert np.abs(K.cpu().numpy() - K0).max() <= tol
     plan.close()
+
+
+@pytest.mark.parametrize("nprim,nwater", [(2, 1), (4, 1), (5, 2), (16, 1)])
+def test_shared_quartets(env, nprim, nwater):
+    """Few quartets of long contractions: neighbouring lanes share a quartet's
+    ket primitive pairs (2, 4, 8, 16 or 32 of them).  Against the oracle, with
+    density screening (lanes of dropped quartets beside others) and J alone."""
+    torch, jk = env
+    elems, xyz = synth.water_lattice(nwater, 77)
+    rng = np.random.default_rng(nprim)
+    shells = []
+    for l in (0, 1, 2, 0):
+        e = np.exp(rng.uniform(np.log(0.1), np.log(500.0), nprim))
+        shells.append((l, e, synth._contract_norm(e, rng.uniform(0.2, 1.0, nprim), l)))
+    mol = synth.build_molecule(synth.BasisTemplate("long", False, {"O": shells, "H": shells[:2]}), elems, xyz)
+    D = synth.random_density(mol.nao, 3 * nwater, 78, 2)
+    Dd = torch.from_numpy(D).cuda()
+    plan = jk.Plan(mol, 1e-13)
+    J0, K0, _ = o.jk(mol, D, 1e-13, mode=1)
+    J, K = plan.execute(Dd)
+    J1, _ = plan.execute(Dd, flags=jk.JK_DO_J)
+    plan.set_density_screening(1e-12)
+    J2, K2 = plan.execute(Dd)
+    torch.cuda.synchronize()
+    for x, y in ((J, J0), (K, K0), (J1, J0), (J2, J0), (K2, K0)):
+        # (the screened contributions are below 1e-12 each, some 1e2 of them per element)
+        assert np.abs(x.cpu().numpy() - y).max() <= 1e-10, (nprim, nwater)
+    plan.close()
