@@ -234,10 +234,14 @@ __global__ void __launch_bounds__(64) k_pair_trim(ShellDev sh, PairRec *pairs, P
     if (lane == 0) pairs[blockIdx.x].npp = kept;
 }
 
-// npp of every pair, for the host's work counts.
+// npp (work counts) and q (screening lists) of every pair, for the host.
 __global__ void k_pair_npp(const PairRec *pairs, int npair, int32_t *npp) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t < npair) npp[t] = pairs[t].npp;
+}
+__global__ void k_pair_q(const PairRec *pairs, int npair, double *q) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < npair) q[t] = pairs[t].q;
 }
 
 // q of each pair from its exported diagonal block (IJ|IJ): sqrt(max_ab |(ab|ab)|)
@@ -630,31 +634,45 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
         (rc = P->put(&d_coords, std::vector<double>(basis->coords, basis->coords + 3 * P->natom))))
         return rc;
     P->sh = ShellDev{d_l, d_np, d_poff, d_atom, d_exps, d_coefs, d_coords};
+    int32_t *d_ids;  // 0, 1, 2, ...: the pairs of a type as an export list
+    {
+        std::vector<int32_t> ids(npair);
+        std::iota(ids.begin(), ids.end(), 0);
+        if ((rc = P->put(&d_ids, ids))) return rc;
+    }
     if ((rc = P->put(&P->d_pairs, P->hpairs))) return rc;
-    if ((rc = P->alloc(&P->d_pp, npp_tot))) return rc;
+    if ((rc = P->alloc(&P->d_pp, npp_tot)) || (rc = P->flush(false))) return rc;
     hipLaunchKernelGGL(k_pair_build, dim3((npair + 127) / 128), dim3(128), 0, 0, P->sh, P->d_pairs, npair, P->d_pp);
     HIPCHK(hipGetLastError());
 
-    // Schwarz factors: exported diagonal blocks (IJ|IJ) per pair type
+    // Schwarz factors: exported diagonal blocks (IJ|IJ) per pair type, one
+    // type after another through one buffer (ordered on the null stream)
+    DevBuf tmp;
+    {
+        size_t bytes = sizeof(double) * npair;
+        for (size_t pt = 0; pt < ptype_first.size(); ++pt) {
+            const PairRec &r0 = P->hpairs[ptype_first[pt]];
+            const size_t nab = (size_t)ncart(P->l[r0.ish]) * ncart(P->l[r0.jsh]);
+            bytes = std::max(bytes, sizeof(double) * ptype_count[pt] * nab * nab);
+        }
+        HIPCHK(hipMalloc(&tmp.p, bytes));
+    }
     for (size_t pt = 0; pt < ptype_first.size(); ++pt) {
         const int first = ptype_first[pt], cnt = ptype_count[pt];
         const PairRec &r0 = P->hpairs[first];
         const int li = P->l[r0.ish], lj = P->l[r0.jsh];
-        const int nab = ncart(li) * ncart(lj);
-        std::vector<int32_t> ids(cnt);
-        std::iota(ids.begin(), ids.end(), first);
-        int32_t *d_ids;
-        double *d_blk;
-        if ((rc = P->put(&d_ids, ids))) return rc;
-        if ((rc = P->alloc(&d_blk, (size_t)cnt * nab * nab))) return rc;
-        if ((rc = launch_export(P, li, lj, li, lj, JK_FP64, d_ids, d_ids, cnt, d_blk, 0))) return rc;
-        hipLaunchKernelGGL(k_schwarz, dim3((cnt + 127) / 128), dim3(128), 0, 0, d_blk, nab, d_ids, cnt, P->d_pairs);
+        if ((rc = launch_export(P, li, lj, li, lj, JK_FP64, d_ids + first, d_ids + first, cnt, tmp.as<double>(), 0))) return rc;
+        hipLaunchKernelGGL(k_schwarz, dim3((cnt + 127) / 128), dim3(128), 0, 0, tmp.as<double>(), ncart(li) * ncart(lj),
+                           d_ids + first, cnt, P->d_pairs);
         HIPCHK(hipGetLastError());
-        HIPCHK(hipDeviceSynchronize());
-        HIPCHK(hipFree(d_blk));
-        P->allocs.erase(std::find(P->allocs.begin(), P->allocs.end(), (void *)d_blk));
     }
-    HIPCHK(hipMemcpy(P->hpairs.data(), P->d_pairs, sizeof(PairRec) * npair, hipMemcpyDeviceToHost));
+    {
+        std::vector<double> q(npair);
+        hipLaunchKernelGGL(k_pair_q, dim3((npair + 255) / 256), dim3(256), 0, 0, P->d_pairs, npair, tmp.as<double>());
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipMemcpy(q.data(), tmp.p, sizeof(double) * npair, hipMemcpyDeviceToHost));
+        for (int p = 0; p < npair; ++p) P->hpairs[p].q = q[p];
+    }
     // renumber the pairs of each type by q descending (ties keep their order),
     // so each type's screening list is a contiguous id range, then rebuild
     // the primitive pairs in that order
@@ -668,12 +686,9 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
     // primitive pairs left per pair (host: work counts only)
     std::vector<int32_t> npp(npair);
     {
-        int32_t *d_npp;
-        HIPCHK(hipMalloc(&d_npp, sizeof(int32_t) * npair));
-        hipLaunchKernelGGL(k_pair_npp, dim3((npair + 255) / 256), dim3(256), 0, 0, P->d_pairs, npair, d_npp);
-        const hipError_t e = hipMemcpy(npp.data(), d_npp, sizeof(int32_t) * npair, hipMemcpyDeviceToHost);
-        (void)hipFree(d_npp);
-        HIPCHK(e);
+        hipLaunchKernelGGL(k_pair_npp, dim3((npair + 255) / 256), dim3(256), 0, 0, P->d_pairs, npair, tmp.as<int32_t>());
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipMemcpy(npp.data(), tmp.p, sizeof(int32_t) * npair, hipMemcpyDeviceToHost));
     }
     P->Qsh.assign((size_t)ns * ns, 0.0);
     double qmax = 0.0;
@@ -687,6 +702,7 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
     std::vector<std::vector<int32_t>> sorted(npt);
     std::vector<std::vector<double>> sortedq(npt);
     std::vector<std::vector<int64_t>> sortedn(npt);  // running sum of npp along sorted
+    std::vector<int> most(npt, 1);                   // largest npp
     std::vector<int32_t *> d_sorted(npt, nullptr);
     for (int pt = 0; pt < npt; ++pt) {
         auto &v = sorted[pt];
@@ -699,6 +715,7 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
         for (int p : v) {
             sortedq[pt].push_back(P->hpairs[p].q);
             sortedn[pt].push_back(sortedn[pt].back() + npp[p]);
+            most[pt] = std::max(most[pt], npp[p]);
         }
         if (!v.empty() && (rc = P->put(&d_sorted[pt], v))) return rc;
     }
@@ -742,15 +759,14 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
             std::vector<int32_t> bl, cn;
             const auto &kq = sortedq[kt];
             int64_t npq_eval = 0;  // primitive quartets evaluated
+            size_t lo = kq.size();
+            bl.reserve(sorted[bt].size());
+            cn.reserve(sorted[bt].size());
             for (size_t i = 0; i < sorted[bt].size(); ++i) {
                 const double qb = sortedq[bt][i];
-                // kets j with qb * kq[j] >= cutoff form a prefix
-                size_t lo = 0, hi = kq.size();
-                while (lo < hi) {
-                    const size_t mid = (lo + hi) / 2;
-                    if (qb * kq[mid] >= cutoff) lo = mid + 1;
-                    else hi = mid;
-                }
+                // kets j with qb * kq[j] >= cutoff form a prefix, no longer
+                // than the one of the bra before (qb descends)
+                while (lo > 0 && !(qb * kq[lo - 1] >= cutoff)) --lo;
                 size_t cnt = lo;
                 if (c.same) cnt = std::min(cnt, i + 1);
                 if (cnt == 0) continue;
@@ -760,8 +776,7 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
                 npq_eval += (int64_t)npp[sorted[bt][i]] * sortedn[kt][cnt];
             }
             if (c.nq == 0) continue;
-            int npk = 1;  // most primitive pairs of a ket
-            for (int p : sorted[kt]) npk = std::max(npk, npp[p]);
+            const int npk = most[kt];
             // tiles of a bra list, per precision in its tile family
             auto place_tiles = [&](const std::vector<int32_t> &cnt, int32_t *(&dst)[2], int (&count)[2], int (&split)[2]) -> int {
                 for (int pr = 0; pr < 2; ++pr) {
@@ -819,7 +834,7 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
                     // row tasks: (list position, first ket, end ket), each long
                     // bra cut into near-equal chunks of at most row_chunk kets
                     for (int f = 0; f < 3; ++f) {
-                        if (!ce.row[f][0]) continue;
+                        if (!ce.row[f][0] || !(c.fam[0] == f + 1 || c.fam[1] == f + 1)) continue;
                         const int gch = g_chunk[class_id(c.li, c.lj, c.lk, c.ll)];
                         const int ch = gch > 0 ? gch : row_chunk(f + 1, c.li, c.lj, c.lk, c.ll);
                         std::vector<int32_t> tasks;
@@ -869,6 +884,7 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
         (rc = P->put(&d_c2s, std::vector<double>(jkt_c2s, jkt_c2s + JKT_C2S_N))))
         return rc;
     P->maps = AoMaps{d_shc, d_cc, d_she, d_ce, d_l, d_aoc, d_aoe, d_c2s};
+    if ((rc = P->flush(true))) return rc;
     HIPCHK(hipDeviceSynchronize());
 
     P->stats.nquartets = nq_tot;

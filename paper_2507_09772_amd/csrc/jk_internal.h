@@ -4,6 +4,9 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstring>
+#include <memory>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -220,11 +223,43 @@ struct jk_plan {
         allocs.push_back(*p);
         return 0;
     }
+    // Lists the host builds: placed one after another in a few device chunks
+    // and sent by flush(), one copy a chunk.  (With an allocation and a copy
+    // for each of the several thousand lists, those took most of
+    // jk_plan_create and of jk_plan_destroy.)
+    struct Chunk {
+        char *dev;
+        std::unique_ptr<char[]> host;
+        size_t size, used, sent;
+    };
+    std::vector<Chunk> chunks;
+    size_t next_chunk = (size_t)256 << 10;
     template <typename T>
     int put(T **p, const std::vector<T> &v) {
-        int rc = alloc(p, v.size());
-        if (rc) return rc;
-        if (!v.empty()) HIPCHK(hipMemcpy(*p, v.data(), sizeof(T) * v.size(), hipMemcpyHostToDevice));
+        const size_t bytes = std::max<size_t>(sizeof(T) * v.size(), 1);
+        if (chunks.empty() || chunks.back().used + bytes > chunks.back().size) {
+            Chunk c{nullptr, nullptr, std::max(bytes, next_chunk), 0, 0};
+            next_chunk = std::min<size_t>(2 * next_chunk, (size_t)8 << 20);
+            c.host.reset(new (std::nothrow) char[c.size]);
+            if (!c.host) return fail(JK_ENOMEM, "host allocation of %zu bytes failed", c.size);
+            const int rc = alloc(&c.dev, c.size);
+            if (rc) return rc;
+            chunks.push_back(std::move(c));
+        }
+        Chunk &c = chunks.back();
+        *p = reinterpret_cast<T *>(c.dev + c.used);
+        if (!v.empty()) std::memcpy(c.host.get() + c.used, v.data(), sizeof(T) * v.size());
+        c.used = std::min((c.used + bytes + 255) / 256 * 256, c.size);
+        return 0;
+    }
+    // Sends what was placed since the last call; done: nothing more will be.
+    int flush(bool done) {
+        for (Chunk &c : chunks)
+            if (c.used > c.sent) {
+                HIPCHK(hipMemcpy(c.dev + c.sent, c.host.get() + c.sent, c.used - c.sent, hipMemcpyHostToDevice));
+                c.sent = c.used;
+            }
+        if (done) chunks.clear();
         return 0;
     }
     ~jk_plan() {
