@@ -1349,7 +1349,21 @@ struct K2Cfg {
     // write to different LDS banks
     static constexpr int SP = C::S % 2 == 0 ? C::S + 1 : C::S;
     static constexpr int TAB = PB * RB * 3 * SP;              // 2-D table entries per quartet
-    // LDS digestion blocks: jij, jkl, kik, kil, kjk, kjl
+    // LDS digestion blocks: jij, jkl, kik, kil, kjk, kjl, each stored with the
+    // larger of its two shells along the fast index, and flushed so: J' and K'
+    // are added to their transposes at the end, so a block may go to (row,
+    // column) or (column, row), and along the larger shell its atomics cover
+    // the fewest cache lines ((fd|ds): 24 runs of up to 10 elements per
+    // quartet instead of 48 of up to 6; the atomic units take about 15 G runs
+    // a second whatever their length: (fs|dp) 45.2 -> 37.3 ms, all of the 8-water
+    // basis C build 1668 -> 1643 ms)
+    static constexpr bool TKJK = C::NJ > C::NK, TKJL = C::NJ > C::NL;  // bra shell along the fast index
+    static __device__ __forceinline__ constexpr int ij(int a, int b) { return O_JIJ + b * C::NI + a; }
+    static __device__ __forceinline__ constexpr int kl(int c, int d) { return O_JKL + d * C::NK + c; }
+    static __device__ __forceinline__ constexpr int ik(int a, int c) { return O_KIK + c * C::NI + a; }
+    static __device__ __forceinline__ constexpr int il(int a, int d) { return O_KIL + d * C::NI + a; }
+    static __device__ __forceinline__ constexpr int jk(int b, int c) { return O_KJK + (TKJK ? c * C::NJ + b : b * C::NK + c); }
+    static __device__ __forceinline__ constexpr int jl(int b, int d) { return O_KJL + (TKJL ? d * C::NJ + b : b * C::NL + d); }
     static constexpr int O_JIJ = 0;
     static constexpr int O_JKL = O_JIJ + C::NI * C::NJ;
     static constexpr int O_KIK = O_JKL + C::NK * C::NL;
@@ -1568,15 +1582,15 @@ __device__ __forceinline__ void k2_body(const JkArgs &a, R *tabs, double *dig, i
                             kjk += v * dil[d];
                             kjlp[bb][d] += v * dik;
                         }
-                        if (a.do_j) atomicAdd(ROW ? &rjij[ia * NJ + b] : &dq[F::O_JIJ + ia * NJ + b], 2.0 * wq * jij);
-                        if (a.do_k) atomicAdd(ROW ? &rJ[b * ncols + cK + ic] : &dq[F::O_KJK + b * NK + ic], wq * kjk);
+                        if (a.do_j) atomicAdd(ROW ? &rjij[ia * NJ + b] : &dq[F::ij(ia, b)], 2.0 * wq * jij);
+                        if (a.do_k) atomicAdd(ROW ? &rJ[b * ncols + cK + ic] : &dq[F::jk(b, ic)], wq * kjk);
                     }
 #pragma unroll
                     for (int d = 0; d < NL; ++d) {
-                        if (a.do_j) atomicAdd(&dq[F::O_JKL + ic * NL + d], 2.0 * wq * jkl[d]);
-                        if (a.do_k) atomicAdd(ROW ? &rI[ia * ncols + cL + d] : &dq[F::O_KIL + ia * NL + d], wq * kil[d]);
+                        if (a.do_j) atomicAdd(&dq[F::kl(ic, d)], 2.0 * wq * jkl[d]);
+                        if (a.do_k) atomicAdd(ROW ? &rI[ia * ncols + cL + d] : &dq[F::il(ia, d)], wq * kil[d]);
                     }
-                    if (a.do_k) atomicAdd(ROW ? &rI[ia * ncols + cK + ic] : &dq[F::O_KIK + ia * NK + ic], wq * kik);
+                    if (a.do_k) atomicAdd(ROW ? &rI[ia * ncols + cK + ic] : &dq[F::ik(ia, ic)], wq * kik);
                 }
                 // K_JL of each quartet: the sum of its lanes' partials (every
                 // slot of the quartet adds to the same elements), reduced
@@ -1602,7 +1616,7 @@ __device__ __forceinline__ void k2_body(const JkArgs &a, R *tabs, double *dig, i
                         if constexpr (ROW) {
                             if (sum != 0.0) atomicAdd(&rJ[b * ncols + (int)dig[q2 * F::DIG + F::O_KJL] + bd % NL], sum);
                         } else {
-                            dig[q2 * F::DIG + F::O_KJL + b * NL + bd % NL] = sum;
+                            dig[q2 * F::DIG + F::jl(b, bd % NL)] = sum;
                         }
                     }
                 }
@@ -1616,12 +1630,21 @@ __device__ __forceinline__ void k2_body(const JkArgs &a, R *tabs, double *dig, i
                         if (v == 0.0) continue;
                         int row, col;
                         double *M;
-                        if (t < F::O_JKL) { row = B.aoi + t / NJ; col = B.aoj + t % NJ; M = Jm; }
-                        else if (t < F::O_KIK) { const int e = t - F::O_JKL; row = Kt.aoi + e / NL; col = Kt.aoj + e % NL; M = Jm; }
-                        else if (t < F::O_KIL) { const int e = t - F::O_KIK; row = B.aoi + e / NK; col = Kt.aoi + e % NK; M = Km; }
-                        else if (t < F::O_KJK) { const int e = t - F::O_KIL; row = B.aoi + e / NL; col = Kt.aoj + e % NL; M = Km; }
-                        else if (t < F::O_KJL) { const int e = t - F::O_KJK; row = B.aoj + e / NK; col = Kt.aoi + e % NK; M = Km; }
-                        else { const int e = t - F::O_KJL; row = B.aoj + e / NL; col = Kt.aoj + e % NL; M = Km; }
+                        if (t < F::O_JKL) { row = B.aoj + t / NI; col = B.aoi + t % NI; M = Jm; }
+                        else if (t < F::O_KIK) { const int e = t - F::O_JKL; row = Kt.aoj + e / NK; col = Kt.aoi + e % NK; M = Jm; }
+                        else if (t < F::O_KIL) { const int e = t - F::O_KIK; row = Kt.aoi + e / NI; col = B.aoi + e % NI; M = Km; }
+                        else if (t < F::O_KJK) { const int e = t - F::O_KIL; row = Kt.aoj + e / NI; col = B.aoi + e % NI; M = Km; }
+                        else if (t < F::O_KJL) {
+                            const int e = t - F::O_KJK;
+                            row = F::TKJK ? Kt.aoi + e / NJ : B.aoj + e / NK;
+                            col = F::TKJK ? B.aoj + e % NJ : Kt.aoi + e % NK;
+                            M = Km;
+                        } else {
+                            const int e = t - F::O_KJL;
+                            row = F::TKJL ? Kt.aoj + e / NJ : B.aoj + e / NL;
+                            col = F::TKJL ? B.aoj + e % NJ : Kt.aoj + e % NL;
+                            M = Km;
+                        }
                         acc_add(a, &M[row * n + col], v);
                     }
                 }
@@ -2072,12 +2095,13 @@ __global__ void __launch_bounds__(NT) jk_k3_row(const JkArgs a_in, const ClsArgs
                 }
             }
             if (a.do_j) {
-                // J'_KL of the wave's quartets into the pair-ordered buffer
+                // J'_KL of the wave's quartets into the pair-ordered buffer, the
+                // quartets (consecutive kets, consecutive addresses) along the lanes
                 wave_sync();
                 for (int t = lane; t < QW * NK * NL; t += 64) {
-                    const int q2 = t / (NK * NL), e = t % (NK * NL);
-                    const double v = jkl[t];
-                    jkl[t] = 0.0;
+                    const int q2 = t % QW, e = t / QW;
+                    const double v = jkl[q2 * (NK * NL) + e];
+                    jkl[q2 * (NK * NL) + e] = 0.0;
                     const int j2 = j0 + q2;
                     if (j2 < cnt && v != 0.0) {
                         const PairRec &K2 = a.pairs[c.ket_list[j2]];
