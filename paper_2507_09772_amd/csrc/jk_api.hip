@@ -441,6 +441,14 @@ static int tile_split(const std::vector<int32_t> &cnt, int npk) {
     }
     return split;
 }
+// Steps of qw kets that one family-2 tile walks: its bra is looked up and read
+// once for all of them.  Up to eight while the class keeps 8192 tiles, several
+// for every place on the device.
+static int tile_steps(const std::vector<int32_t> &cnt, int qw) {
+    int64_t n = 0;
+    for (int32_t k : cnt) n += (k + qw - 1) / qw;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(8, n / 8192));
+}
 // First tile of every bra (off), for per quartets a tile; returns the tiles.
 static int64_t tile_offsets(const std::vector<int32_t> &cnt, int per, std::vector<int32_t> *off) {
     int64_t tiles = 0;
@@ -475,6 +483,7 @@ static int place_classes(jk_plan *P) {
             b.tile_off = c.d_tile[pr];
             b.ctr = work_slot(ci, pr, WORK_TILES);
             b.split = c.tsplit[pr];
+            b.steps = c.tsteps[pr];
             ca[work_slot(ci, pr, WORK_TILES)] = b;
             b.ctr = work_slot(ci, pr, WORK_ROWS);
             b.row_pos = c.d_rowc[c.fam[pr] - 1];
@@ -489,6 +498,7 @@ static int place_classes(jk_plan *P) {
             b.tile_off = c.d_stile[pr];
             b.ctr = work_slot(ci, pr, WORK_TILES);
             b.split = c.tssplit[pr];
+            b.steps = c.tssteps[pr];
             ca[work_slot(ci, pr, WORK_STILES)] = b;
         }
         int &k = of[class_id(c.li, c.lj, c.lk, c.ll)];
@@ -778,17 +788,20 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
             if (c.nq == 0) continue;
             const int npk = most[kt];
             // tiles of a bra list, per precision in its tile family
-            auto place_tiles = [&](const std::vector<int32_t> &cnt, int32_t *(&dst)[2], int (&count)[2], int (&split)[2]) -> int {
+            auto place_tiles = [&](const std::vector<int32_t> &cnt, int32_t *(&dst)[2], int (&count)[2], int (&split)[2],
+                                   int (&steps)[2]) -> int {
                 for (int pr = 0; pr < 2; ++pr) {
                     const int f = c.tile_family(pr);
                     split[pr] = f == 1 && pr == 0 ? tile_split(cnt, npk) : 0;
+                    const int qw = quartets_per_tile(f, c.li, c.lj, c.lk, c.ll);
+                    steps[pr] = f == 2 ? tile_steps(cnt, qw) : 1;
                     if (pr == 1 && c.tile_family(0) == f && split[0] == 0) {
                         dst[1] = dst[0];
                         count[1] = count[0];
                         continue;
                     }
                     std::vector<int32_t> off;
-                    const int64_t n = tile_offsets(cnt, quartets_per_tile(f, c.li, c.lj, c.lk, c.ll) >> split[pr], &off);
+                    const int64_t n = tile_offsets(cnt, f == 1 ? qw >> split[pr] : qw * steps[pr], &off);
                     if (n > INT32_MAX) return fail(JK_EUNSUPPORTED, "class (%d%d|%d%d) has too many quartets", c.li, c.lj, c.lk, c.ll);
                     count[pr] = (int)n;
                     const int rc2 = P->put(&dst[pr], off);
@@ -802,7 +815,7 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
             c.npq = c.nq * c.npb * c.npk;
             c.flops = (double)npq_eval * flops_prim(c.li, c.lj, c.lk, c.ll) + (double)c.nq * flops_digest(c.li, c.lj, c.lk, c.ll);
             if ((rc = P->put(&c.d_bra, bl)) || (rc = P->put(&c.d_cnt, cn))) return rc;
-            if ((rc = place_tiles(cn, c.d_tile, c.ntiles, c.tsplit))) return rc;
+            if ((rc = place_tiles(cn, c.d_tile, c.ntiles, c.tsplit, c.tsteps))) return rc;
             c.d_ket = d_sorted[kt];
             // row mode split: bras with a long ket prefix get a workgroup each
             {
@@ -852,7 +865,7 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
                     }
                     if (c.nsbra > 0) {
                         if ((rc = P->put(&c.d_sbra, sb)) || (rc = P->put(&c.d_scnt, scn))) return rc;
-                        if ((rc = place_tiles(scn, c.d_stile, c.nstiles, c.tssplit))) return rc;
+                        if ((rc = place_tiles(scn, c.d_stile, c.nstiles, c.tssplit, c.tssteps))) return rc;
                     }
                 } else {
                     c.nrow = 0;

@@ -323,6 +323,7 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                 if (kind == 0) {  // (f <= 2 here)
                     k.tile_off = c.d_tile[pr];
                     k.split = c.tsplit[pr];
+                    k.steps = c.tsteps[pr];
                 }
                 k.ket_list = c.d_ket;
                 k.npb = c.npb;

@@ -93,13 +93,17 @@ JK_HD constexpr int k2_qw(int li, int lj, int lk, int ll) {
     return k2_slots(li, lj, lk, ll) >= 64 ? 1 : 64 / k2_slots(li, lj, lk, ll);
 }
 
+// Lanes that work on one wave's quartets in a family-2 tile: a wave while the
+// slots fit one, otherwise as many waves as they need.
+JK_HD constexpr int k2_lanes(int li, int lj, int lk, int ll) { return (k2_slots(li, lj, lk, ll) + 63) / 64 * 64; }
+
 // Row mode: kets per workgroup task.  Long bras are cut into chunks so one
 // bra's kets spread over several workgroups (family 1 computes 256 kets
 // per pass, family 2 four waves of k2_qw quartets).
 JK_HD constexpr int row_chunk(int fam, int li, int lj, int lk, int ll) {
     return fam == 1 ? 2048 : fam == 2 ? 256 * k2_qw(li, lj, lk, ll) : 256 * k3_qw(li);
 }
-// Quartets per wave-tile of a family.
+// Quartets per wave-tile of a family (family 2: per step of a tile).
 JK_HD constexpr int quartets_per_tile(int fam, int li, int lj, int lk, int ll) {
     return fam == 1 ? 64 : k2_qw(li, lj, lk, ll);
 }
@@ -146,6 +150,7 @@ struct ClsArgs {
     int32_t ncolK, ncolL, seg_same;
     int32_t ctr;  // its evaluated-quartet counters: slot of JkArgs::nsel
     int32_t split;  // family-1 tiles: 2^split lanes share a quartet's ket primitive pairs
+    int32_t steps;  // family-2 tiles: steps of k2_qw kets a tile covers
 };
 
 // The work of one launch: units (tiles or row tasks) base[k] .. base[k+1] - 1

@@ -500,6 +500,56 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// v + (the other lane's v) along a row of 16 lanes rotated by N: after 8, 4,
+// 2 and 1 every lane of the row holds the row's sum.
+template <int N>
+__device__ __forceinline__ double row_ror_add(double v) {
+    const unsigned long long b = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0u, (unsigned)b, 0x120 | N, 0xf, 0xf, true);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0u, (unsigned)(b >> 32), 0x120 | N, 0xf, 0xf, true);
+    return v + __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+// One step of the reduction of two values at once: the upper half (ROW16:
+// the odd rows of 16 lanes) of x changes places with the lower half (even
+// rows) of y, so that one addition leaves x's partial sums in the lower half
+// and y's in the upper.
+template <bool ROW16>
+__device__ __forceinline__ double swap_add(double x, double y) {
+    const unsigned long long a = __double_as_longlong(x), b = __double_as_longlong(y);
+    auto sw = [](unsigned u, unsigned v) {
+        if constexpr (ROW16) return __builtin_amdgcn_permlane16_swap(u, v, false, false);
+        else return __builtin_amdgcn_permlane32_swap(u, v, false, false);
+    };
+    const auto lo = sw((unsigned)a, (unsigned)b), hi = sw((unsigned)(a >> 32), (unsigned)(b >> 32));
+    const unsigned long long p = ((unsigned long long)hi[0] << 32) | lo[0], q = ((unsigned long long)hi[1] << 32) | lo[1];
+    return __longlong_as_double((long long)p) + __longlong_as_double((long long)q);
+}
+// Sums of N values over the wave, all lanes active: add(e, sum of v[e]) is
+// called by one lane per element.  The values are halved twice by lane swaps (a quarter of them is left per row of
+// 16 lanes) and then rotated within the rows: about five vector instructions
+// per value and no LDS traffic, against twelve LDS permutes and six additions
+// of a butterfly over each value.
+template <int N, typename Add>
+__device__ __forceinline__ void wave_sums(double (&v)[N], Add &&add) {
+    constexpr int H = (N + 1) / 2, Q = (H + 1) / 2;
+    const int lane = lane_index();
+    double h[H];
+#pragma unroll
+    for (int t = 0; t < H; ++t) h[t] = swap_add<false>(v[t], H + t < N ? v[H + t] : 0.0);
+#pragma unroll
+    for (int t = 0; t < Q; ++t) {
+        double r = swap_add<true>(h[t], Q + t < H ? h[Q + t] : 0.0);
+        r = row_ror_add<8>(r);
+        r = row_ror_add<4>(r);
+        r = row_ror_add<2>(r);
+        r = row_ror_add<1>(r);
+        // rows 0, 1 (lower half): elements t, Q + t; rows 2, 3: those of the upper half
+        const int e = (lane >= 32 ? H : 0) + ((lane & 16) ? Q : 0) + t;
+        // (Q + t >= H: padding)
+        if ((lane & 15) == 0 && e < N && (Q + t < H || !(lane & 16))) add(e, r);
+    }
+}
+
 __device__ __forceinline__ int wave_max(int v) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, 64));
@@ -1301,17 +1351,29 @@ jk_k1_row(const JkArgs a, const ClsArgs *__restrict__ cls, const ClsGroup grp, c
 // its elements from LDS.  Digestion: per slot partial sums, reduced across
 // the group in LDS, then one FP64 global atomic per block element.
 // ===========================================================================
-template <int LI, int LJ, int LK, int LL>
+// ROW: one wave per quartet or several quartets per wave (row kernels, whose
+// waves walk their quartets independently).  Tiles give a quartet with more
+// than 64 slots as many waves as its slots need: they share one set of
+// tables (which is what limits the workgroups per CU), a lane holds one slot,
+// and most classes need one pass, so the tables are built once.  With one
+// wave, (gf|fd) ran 3 slots per lane in 5 passes over 2 root blocks, each
+// pass building its tables anew with 9 of 64 lanes, at half a wave per SIMD:
+// its class 65.4 -> 25.1 ms, (gf|ff) 61.3 -> 16.7, (ff|fd) 34.3 -> 23.4, the whole
+// 8-water basis C build 1643 -> 1183 ms (with the steps of a tile).
+template <int LI, int LJ, int LK, int LL, bool ROW>
 struct K2Cfg {
     using C = Cls<LI, LJ, LK, LL>;
     static constexpr int NSLOT = C::NI * C::NK;
     static constexpr int QW = k2_qw(LI, LJ, LK, LL);
-    static constexpr int LPQ = QW > 1 ? NSLOT : 64;          // lanes per quartet
+    static constexpr int NTQ = ROW ? 64 : k2_lanes(LI, LJ, LK, LL);  // lanes of a group
+    static constexpr int NWQ = NTQ / 64;
+    static constexpr int LPQ = QW > 1 ? NSLOT : NTQ;         // lanes per quartet
     static constexpr int SPL = (NSLOT + LPQ - 1) / LPQ;       // slots per lane
-    // b-chunk per pass: keep SPL * CB * NL accumulators <= 48
+    // b-chunk per pass: keep SPL * CB * NL accumulators <= 48 (60 with
+    // several waves, where a pass less also saves its table build)
     static constexpr int cb_() {
         int cb = C::NJ;
-        while (cb > 1 && SPL * cb * C::NL > 48) --cb;
+        while (cb > 1 && SPL * cb * C::NL > (NWQ > 1 ? 60 : 48)) --cb;
         return cb;
     }
     static constexpr int CB = cb_();
@@ -1371,11 +1433,14 @@ struct K2Cfg {
     static constexpr int O_KJK = O_KIL + C::NI * C::NL;
     static constexpr int O_KJL = O_KJK + C::NJ * C::NK;
     static constexpr int DIG = O_KJL + C::NJ * C::NL;
-    // per wave: the QW digestion blocks, then every lane's partial K_JL
-    // sums of a pass ([lane][b in pass][d]), reduced over the slots without
-    // atomics
-    static constexpr int PARTW = 64 * CB * C::NL;
-    static constexpr int DIGW = QW * DIG + PARTW;
+    // per group: the digestion blocks of its quartets (one per wave where a
+    // quartet has several waves, added in a fixed order when flushed); with
+    // several quartets per wave then every lane's partial K_JL sums of a pass
+    // ([lane][b in pass][d]), reduced over the slots without atomics (else
+    // they are added across the wave)
+    static constexpr int NDIG = QW > 1 ? QW : NWQ;
+    static constexpr int PARTW = QW > 1 ? 64 * CB * C::NL : 0;
+    static constexpr int DIGW = NDIG * DIG + PARTW;
     // table index [ax][cx][bx][dx]
     static __device__ __forceinline__ constexpr int tix(int ax, int bx, int cx, int dx) {
         return ((ax * (LK + 1) + cx) * (LJ + 1) + bx) * (LL + 1) + dx;
@@ -1394,10 +1459,14 @@ template <int LI, int LJ, int LK, int LL, typename R, int MODE, bool ROW = false
 __device__ __forceinline__ void k2_body(const JkArgs &a, R *tabs, double *dig, int bra, int ket, bool valid, double wq,
                                         int64_t gq, double *rows = nullptr, int ncols = 0, int segL = 0) {
     using C = Cls<LI, LJ, LK, LL>;
-    using F = K2Cfg<LI, LJ, LK, LL>;
+    using F = K2Cfg<LI, LJ, LK, LL, ROW>;
     constexpr int NI = C::NI, NJ = C::NJ, NK = C::NK, NL = C::NL, NR = C::NR, S = F::SP;
-    constexpr int QW = F::QW, LPQ = F::LPQ, SPL = F::SPL, CB = F::CB, NPASS = F::NPASS, PB = F::PB;
-    const int lane = lane_index();
+    constexpr int QW = F::QW, LPQ = F::LPQ, SPL = F::SPL, CB = F::CB, NPASS = F::NPASS, PB = F::PB, NTQ = F::NTQ;
+    const int lane = NTQ == 64 ? lane_index() : (int)threadIdx.x;  // lane of the group
+    auto group_sync = [] {
+        if constexpr (F::NWQ > 1) __syncthreads();
+        else wave_sync();
+    };
     const int q = QW > 1 ? lane / LPQ : 0;
     const int sl = QW > 1 ? lane % LPQ : lane;
     const bool lane_used = q < QW;
@@ -1406,10 +1475,10 @@ __device__ __forceinline__ void k2_body(const JkArgs &a, R *tabs, double *dig, i
     const PairRec Kt = a.pairs[ket];
     const int npb = B.npp;
     const int npq = npb * Kt.npp;
-    const int npq_max = wave_max(npq);
+    const int npq_max = QW > 1 ? wave_max(npq) : __builtin_amdgcn_readfirstlane(npq);
 
     R *tq = tabs + qq * F::TAB;
-    double *dq = dig + qq * F::DIG;
+    double *dq = dig + (F::NWQ > 1 ? (int)(threadIdx.x >> 6) : qq) * F::DIG;
 
     int sa[SPL], sc[SPL];
     bool sv[SPL];
@@ -1460,7 +1529,7 @@ __device__ __forceinline__ void k2_body(const JkArgs &a, R *tabs, double *dig, i
             constexpr int RB = F::RB;
             const int r0 = rb * RB, nrb = NR - r0 < RB ? NR - r0 : RB;  // roots of this block
             if (build) {
-                wave_sync();
+                group_sync();
                 // one task per (primitive quartet of the batch, root, direction)
                 for (int t = sl; t < PB * 3 * nrb && lane_used; t += LPQ) {
                     const int p = t / (3 * nrb), t2 = t - p * (3 * nrb);
@@ -1491,7 +1560,7 @@ __device__ __forceinline__ void k2_body(const JkArgs &a, R *tabs, double *dig, i
                     rys2d<LI, LJ, LK, LL, R>(c00, c00p, b00, b10, b01, abx, cdx, sc2,
                                              [&](int ia, int ib2, int ic, int id, R v) { dst[F::tix(ia, ib2, ic, id)] = v; });
                 }
-                wave_sync();
+                group_sync();
             }
             for (int p = 0; p < PB; ++p) {
             if (it0 + p >= nit) break;  // uniform in the wave
@@ -1540,9 +1609,9 @@ __device__ __forceinline__ void k2_body(const JkArgs &a, R *tabs, double *dig, i
             for (int s = 0; s < a.nset; ++s) {
                 const double *D = a.D + s * a.mstride;
                 double *rI = rows + s * per_set, *rJ = rI + NI * ncols, *rjij = rI + (NI + NJ) * ncols;
-                wave_sync();
-                for (int t = lane; t < QW * F::DIG; t += 64) dig[t] = 0.0;
-                wave_sync();
+                group_sync();
+                for (int t = lane; t < F::NDIG * F::DIG; t += NTQ) dig[t] = 0.0;
+                group_sync();
                 double kjlp[CB][NL];
 #pragma unroll
                 for (int bb = 0; bb < CB; ++bb)
@@ -1593,11 +1662,28 @@ __device__ __forceinline__ void k2_body(const JkArgs &a, R *tabs, double *dig, i
                     if (a.do_k) atomicAdd(ROW ? &rI[ia * ncols + cK + ic] : &dq[F::ik(ia, ic)], wq * kik);
                 }
                 // K_JL of each quartet: the sum of its lanes' partials (every
-                // slot of the quartet adds to the same elements), reduced
-                // through LDS without atomics; in row mode one LDS atomic per
-                // element then adds it to the bra's K row, at the quartet's
-                // ket column (kept in the quartet's unused K_JL digestion slot)
-                if (a.do_k) {
+                // slot of the quartet adds to the same elements); in row mode
+                // one LDS atomic per element then adds it to the bra's K row
+                if (a.do_k && QW == 1) {
+                    double kv[CB * NL];
+#pragma unroll
+                    for (int bb = 0; bb < CB; ++bb)
+#pragma unroll
+                        for (int d = 0; d < NL; ++d) kv[bb * NL + d] = wq * kjlp[bb][d];
+                    wave_sums<CB * NL>(kv, [&](int e, double x) {
+                        const int b = pass * CB + e / NL;
+                        if (b >= NJ) return;
+                        if constexpr (ROW) {
+                            if (x != 0.0) atomicAdd(&rJ[b * ncols + cL + e % NL], x);
+                        } else {
+                            dq[F::jl(b, e % NL)] = x;
+                        }
+                    });
+                }
+                // (several quartets per wave: reduced through LDS without
+                // atomics, at the quartet's ket column, which is kept in the
+                // quartet's unused K_JL digestion slot)
+                if (a.do_k && QW > 1) {
                     double *part = dig + QW * F::DIG;
                     if constexpr (ROW) {
                         if (lane_used && sl == 0) dq[F::O_KJL] = (double)cL;
@@ -1606,7 +1692,7 @@ __device__ __forceinline__ void k2_body(const JkArgs &a, R *tabs, double *dig, i
                     for (int bb = 0; bb < CB; ++bb)
 #pragma unroll
                         for (int d = 0; d < NL; ++d) part[lane * (CB * NL) + bb * NL + d] = wq * kjlp[bb][d];
-                    wave_sync();
+                    group_sync();
                     for (int t = lane; t < QW * CB * NL; t += 64) {
                         const int q2 = t / (CB * NL), bd = t % (CB * NL);
                         const int b = pass * CB + bd / NL;
@@ -1620,13 +1706,18 @@ __device__ __forceinline__ void k2_body(const JkArgs &a, R *tabs, double *dig, i
                         }
                     }
                 }
-                wave_sync();
+                group_sync();
                 if (lane_used && valid) {
                     double *Jm = a.J + s * a.mstride;
                     double *Km = a.K + s * a.mstride;
                     const int t0 = ROW ? F::O_JKL : 0, t1 = ROW ? F::O_KIK : F::DIG;
                     for (int t = t0 + sl; t < t1; t += LPQ) {
-                        const double v = dq[t];
+                        double v = dq[t];
+                        if constexpr (F::NWQ > 1) {
+                            v = dig[t];
+#pragma unroll
+                            for (int w2 = 1; w2 < F::NWQ; ++w2) v += dig[w2 * F::DIG + t];
+                        }
                         if (v == 0.0) continue;
                         int row, col;
                         double *M;
@@ -1653,33 +1744,38 @@ __device__ __forceinline__ void k2_body(const JkArgs &a, R *tabs, double *dig, i
     }
 }
 
-// One tile (QW kets of one bra) for the one-wave workgroup, expanded in
-// place in each kernel.  As a helper function taking the LDS arrays as
+// One tile (c.steps steps of QW kets of one bra) for the workgroup, expanded
+// in place in each kernel.  As a helper function taking the LDS arrays as
 // pointers, the compiler kept the large FP64 classes' accumulators in
 // scratch (four times the private memory of the in-place form) and the
-// (ff|ff) kernel returned wrong values.
-#define JK_K2_TILE(a, c, wave)                                                  \
+// (ff|ff) kernel returned wrong values.  Everything that decides a branch is
+// uniform in the workgroup (one quartet where it has several waves).
+#define JK_K2_TILE(a, c, tile)                                                  \
     do {                                                                        \
-        const int i_ = tile_bra((c).tile_off, (c).nbra, (wave));                \
-        const int j0_ = ((wave) - (c).tile_off[i_]) * QW;                       \
-        const int j_ = j0_ + qq;                                                \
+        const int i_ = tile_bra((c).tile_off, (c).nbra, (tile));                \
+        const int jb_ = ((tile) - (c).tile_off[i_]) * (QW * (c).steps);         \
         const int cnt_ = (c).bra_cnt[i_];                                       \
-        bool valid_ = lane_used && j_ < cnt_;                                   \
+        const int je_ = min(cnt_, jb_ + QW * (c).steps);                        \
         const int bra_ = (c).bra_list[i_];                                      \
-        if (!prefix_selectable((a), (a).pairs[bra_].q, (a).pairs[(c).ket_list[j0_]].q)) break; \
-        const int ket_ = (c).ket_list[j_ < cnt_ ? j_ : cnt_ - 1];               \
         const PairRec &B_ = (a).pairs[bra_];                                    \
-        const PairRec &K_ = (a).pairs[ket_];                                    \
-        const double wq_ = pair_weight(bra_, ket_, B_, K_);                     \
-        screen_quartet((a), B_, K_, valid_);                                    \
-        const int n_ = count_selected(valid_ && sl == 0);                       \
-        add_count((a), (c), n_);                                                \
-        if (n_ > 0) k2_body<LI, LJ, LK, LL, R, MODE_JK>((a), tabs, dig, bra_, ket_, valid_, wq_, 0); \
+        for (int j0_ = jb_; j0_ < je_; j0_ += QW) {                             \
+            if (!prefix_selectable((a), B_.q, (a).pairs[(c).ket_list[j0_]].q)) break; \
+            const int j_ = j0_ + qq;                                            \
+            bool valid_ = lane_used && j_ < cnt_;                               \
+            const int ket_ = (c).ket_list[j_ < cnt_ ? j_ : cnt_ - 1];           \
+            const PairRec &K_ = (a).pairs[ket_];                                \
+            const double wq_ = pair_weight(bra_, ket_, B_, K_);                 \
+            screen_quartet((a), B_, K_, valid_);                                \
+            const int n_ = QW > 1 ? count_selected(valid_ && sl == 0) : (valid_ ? 1 : 0); \
+            if (n_ == 0) continue;                                              \
+            if (threadIdx.x < 64) add_count((a), (c), n_);                      \
+            k2_body<LI, LJ, LK, LL, R, MODE_JK>((a), tabs, dig, bra_, ket_, valid_, wq_, 0); \
+        }                                                                       \
     } while (0)
 
 template <int LI, int LJ, int LK, int LL, typename R, int MODE>
-__global__ void __launch_bounds__(64) jk_k2(const JkArgs a, const ClsArgs *__restrict__ cls, const ClsGroup grp) {
-    using F = K2Cfg<LI, LJ, LK, LL>;
+__global__ void __launch_bounds__(k2_lanes(LI, LJ, LK, LL)) jk_k2(const JkArgs a, const ClsArgs *__restrict__ cls, const ClsGroup grp) {
+    using F = K2Cfg<LI, LJ, LK, LL, false>;
     constexpr int QW = F::QW, LPQ = F::LPQ;
     __shared__ R tabs[QW * F::TAB];
     __shared__ double dig[F::DIGW];
@@ -1707,7 +1803,7 @@ __global__ void __launch_bounds__(64) jk_k2(const JkArgs a, const ClsArgs *__res
 // DIGW doubles, then (waves) x QW x TAB reals.
 template <int LI, int LJ, int LK, int LL>
 struct K2RowLds {
-    using F = K2Cfg<LI, LJ, LK, LL>;
+    using F = K2Cfg<LI, LJ, LK, LL, true>;
     // per wave of the workgroup
     template <typename R>
     static constexpr size_t fixed() { return (size_t)F::DIGW * sizeof(double) + (size_t)F::QW * F::TAB * sizeof(R); }
@@ -1723,7 +1819,7 @@ template <int LI, int LJ, int LK, int LL, typename R, int NT, bool BATCH>
 __global__ void __launch_bounds__(NT) jk_k2_row(const JkArgs a_in, const ClsArgs *__restrict__ cls, const ClsGroup grp,
                                                 const BatchDesc *__restrict__ descs, int ndesc) {
     using C = Cls<LI, LJ, LK, LL>;
-    using F = K2Cfg<LI, LJ, LK, LL>;
+    using F = K2Cfg<LI, LJ, LK, LL, true>;
     constexpr int NI = C::NI, NJ = C::NJ, NAB = C::NAB;
     constexpr int QW = F::QW, LPQ = F::LPQ, NW = NT / 64;
     extern __shared__ double smem2[];
@@ -2154,8 +2250,8 @@ __global__ void __launch_bounds__(256) jk_k1_batch(const BatchDesc *__restrict__
 }
 
 template <int LI, int LJ, int LK, int LL, typename R>
-__global__ void __launch_bounds__(64) jk_k2_batch(const BatchDesc *__restrict__ descs, int ndesc, int total) {
-    using F = K2Cfg<LI, LJ, LK, LL>;
+__global__ void __launch_bounds__(k2_lanes(LI, LJ, LK, LL)) jk_k2_batch(const BatchDesc *__restrict__ descs, int ndesc, int total) {
+    using F = K2Cfg<LI, LJ, LK, LL, false>;
     constexpr int QW = F::QW, LPQ = F::LPQ;
     __shared__ R tabs[QW * F::TAB];
     __shared__ double dig[F::DIGW];

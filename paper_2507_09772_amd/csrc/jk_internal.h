@@ -155,6 +155,7 @@ struct ClassTask {
     // tiles per precision (in tile_family(pr))
     int ntiles[2] = {0, 0};
     int tsplit[2] = {0, 0}, tssplit[2] = {0, 0};  // lanes (log2) per quartet of family-1 tiles, all and short
+    int tsteps[2] = {1, 1}, tssteps[2] = {1, 1};  // steps per family-2 tile, all and short
     int tile_family(int pr) const { return fam[pr] == 3 ? tile_fallback(li, lj, lk, ll) : fam[pr]; }
     int64_t nq, npq;
     double flops;

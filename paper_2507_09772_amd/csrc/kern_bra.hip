@@ -101,7 +101,7 @@ static hipError_t launch_row2_batch(const BatchDesc *d, int ndesc, int total, si
 template <int LI, int LJ, int LK, int LL, typename R>
 static hipError_t launch_k2(const JkArgs &a, const ClsArgs *cls, const ClsGroup &g, size_t, hipStream_t s) {
     if (g.base[g.n] <= 0) return hipSuccess;
-    hipLaunchKernelGGL((jk_k2<LI, LJ, LK, LL, R, MODE_JK>), dim3(g.base[g.n]), dim3(64), 0, s, a, cls, g);
+    hipLaunchKernelGGL((jk_k2<LI, LJ, LK, LL, R, MODE_JK>), dim3(g.base[g.n]), dim3(k2_lanes(LI, LJ, LK, LL)), 0, s, a, cls, g);
     return hipGetLastError();
 }
 
@@ -109,8 +109,8 @@ template <int LI, int LJ, int LK, int LL, typename R>
 static hipError_t export_k2(const JkArgs &a, hipStream_t s) {
     constexpr int QW = k2_qw(LI, LJ, LK, LL);
     if (a.nq <= 0) return hipSuccess;
-    hipLaunchKernelGGL((jk_k2<LI, LJ, LK, LL, R, MODE_EXPORT>), dim3((a.nq + QW - 1) / QW), dim3(64), 0, s, a,
-                       (const ClsArgs *)nullptr, ClsGroup{});
+    hipLaunchKernelGGL((jk_k2<LI, LJ, LK, LL, R, MODE_EXPORT>), dim3((a.nq + QW - 1) / QW),
+                       dim3(k2_lanes(LI, LJ, LK, LL)), 0, s, a, (const ClsArgs *)nullptr, ClsGroup{});
     return hipGetLastError();
 }
 
@@ -125,7 +125,7 @@ static hipError_t launch_k1_batch(const BatchDesc *d, int ndesc, int total, hipS
 template <int LI, int LJ, int LK, int LL, typename R>
 static hipError_t launch_k2_batch(const BatchDesc *d, int ndesc, int total, hipStream_t s) {
     if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL((jk_k2_batch<LI, LJ, LK, LL, R>), dim3(total), dim3(64), 0, s, d, ndesc, total);
+    hipLaunchKernelGGL((jk_k2_batch<LI, LJ, LK, LL, R>), dim3(total), dim3(k2_lanes(LI, LJ, LK, LL)), 0, s, d, ndesc, total);
     return hipGetLastError();
 }
 
