@@ -178,7 +178,7 @@ def kernel_name(t):
     prec = "double" if t.precision == 0 else "float"
     cls = f"{t.li}, {t.lj}, {t.lk}, {t.ll}"
     if t.kind in (1, 3):
-        return f"jk_k{t.family}_row<{cls}, {prec}, {256 if t.kind == 1 else 64}, false>"
+        return f"jk_k{t.family}_row<{cls}, {prec}, {256 if t.kind == 1 else 64}>"
     return f"jk_k{t.family}<{cls}, {prec}, 0>"
 
 

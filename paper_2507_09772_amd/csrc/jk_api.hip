@@ -1397,7 +1397,7 @@ int execute_impl(jk_plan *P, const double *D, int32_t nset, int32_t flags, int32
         }
         a.sel = l.sel;
         if ((rc = mark())) return rc;
-        HIPCHK(l.fn(a, P->d_cls, l.g, l.lds, s));
+        HIPCHK(l.fn(a, P->d_cls, l.g, Batch{}, l.g.base[l.g.n], l.lds, s));
     }
     s = s0;
     for (int k = 1; k < nst; ++k) {

@@ -102,7 +102,7 @@ __global__ void kb_zero_u64(unsigned long long *p, int n) {
 struct Group {
     int cid, fam;
     int pr, sel;       // kernel precision (0 FP64, 1 FP32); quartet selection (SEL_*)
-    int kind;          // 0: tiles, 1: 64-lane row tasks
+    int kind;          // 0: tiles, 1: row tasks of 64 lanes, 2: of 256 lanes
     size_t lds;        // row tasks: largest dynamic LDS over the descriptors
     int first, count;
     int total_tiles;
@@ -209,8 +209,8 @@ static int record(jk_batch *b) {
         const Group &g = b->groups[gi];
         const ClassEntry &e = g_classes[g.cid];
         hipStream_t bs = b->branch[(br + gi) % b->nbranch];
-        if (g.kind == 1) HIPCHK(e.batch_row[g.fam - 1][g.pr](b->d_desc + g.first, g.count, g.total_tiles, g.lds, bs));
-        else HIPCHK(e.batch[g.fam - 1][g.pr](b->d_desc + g.first, g.count, g.total_tiles, bs));
+        const Launcher fn = (g.kind == 0 ? e.tiles : g.kind == 1 ? e.srow : e.row)[g.fam - 1][g.pr];
+        HIPCHK(fn(JkArgs{}, nullptr, ClsGroup{}, Batch{b->d_desc + g.first, g.count}, g.total_tiles, g.lds, bs));
     }
     for (int k = 1; k < b->nbranch; ++k) {
         HIPCHK(hipEventRecord(b->join[k], b->branch[k]));
@@ -269,8 +269,11 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
 
     // descriptors grouped by (class, family, kind, precision, selection);
     // heavy molecules first.  Unless row mode is off for the class, every
-    // bra runs as 64-lane row tasks (K rows in LDS): the small molecules of
-    // a batch have few long bras, and per-quartet K atomics would dominate.
+    // bra runs as row tasks (K rows in LDS; per-quartet K atomics would
+    // dominate): the long ones in 256-lane workgroups, whose four waves share
+    // one set of rows, the short ones in 64-lane ones.  (All of them in 64
+    // lanes, the rows of four densities left room for about three waves a
+    // CU.)
     // Mixed precision: two descriptors per (molecule, class), the
     // single-precision pass over the quartets below the threshold and the
     // double-precision pass over the rest.
@@ -308,9 +311,13 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                 const ClassEntry &ce = g_classes[class_id(c.li, c.lj, c.lk, c.ll)];
                 const int ncols = c.ncolK + (c.seg_same ? 0 : c.ncolL);
                 const size_t lds1 = row_lds_bytes(ce, f, pr, c.li, c.lj, nset, ncols, 1, c.npb);
-                const int kind = c.row_ok[pr] && ce.batch_row[f - 1][pr] && lds1 <= (size_t)ROW_LDS_MAX ? 1 : 0;
+                const size_t lds4 = row_lds_bytes(ce, f, pr, c.li, c.lj, nset, ncols, 4, c.npb);
+                const bool rows = c.row_ok[pr] && ce.srow[f - 1][pr] && lds1 <= (size_t)ROW_LDS_MAX;
+                const bool wide = rows && !c.h_rowc[f - 1].empty() && lds4 <= (size_t)ROW_LDS_MAX;
                 // tiles of a family-3 class run in its fallback family
-                if (kind == 0) f = c.tile_family(pr);
+                if (!rows) f = c.tile_family(pr);
+                // (classes with a g shell have no 64-lane row kernels)
+                if (c.li > 3) return fail(JK_EUNSUPPORTED, "class (%d%d|%d%d) has no batched kernel", c.li, c.lj, c.lk, c.ll);
                 if (c.nq <= 0) continue;
                 BatchDesc d{};
                 JkArgs &a = d.a;
@@ -320,11 +327,6 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                 k.bra_list = c.d_bra;
                 k.bra_cnt = c.d_cnt;
                 k.nbra = c.nbra;
-                if (kind == 0) {  // (f <= 2 here)
-                    k.tile_off = c.d_tile[pr];
-                    k.split = c.tsplit[pr];
-                    k.steps = c.tsteps[pr];
-                }
                 k.ket_list = c.d_ket;
                 k.npb = c.npb;
                         a.nq = (int32_t)c.nq;
@@ -345,26 +347,47 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                 a.sel = sel;
                 a.mix_thr = mix_threshold;
                 a.tab = P->tab;
-                d.pad[1] = kind == 0 ? c.ntiles[pr] : 0;  // work units (tiles or row tasks)
-                if (kind == 1) {
-                    // every bra of the class: long bras in chunks, short ones whole
-                    const size_t first = alltasks.size();
-                    alltasks.insert(alltasks.end(), c.h_rowc[f - 1].begin(), c.h_rowc[f - 1].end());
-                    alltasks.insert(alltasks.end(), c.h_srowt.begin(), c.h_srowt.end());
-                    d.pad[1] = (int32_t)((alltasks.size() - first) / 3);
-                    d.pad[2] = (int32_t)first;  // offset into the task buffer (host only)
-                    k.tshK = c.d_tshK;
-                    k.tshL = c.d_tshL;
-                    k.ncolK = c.ncolK;
-                    k.ncolL = c.ncolL;
-                    k.seg_same = c.seg_same;
-                    if (alltasks.size() > (size_t)INT32_MAX) return fail(JK_EINVAL, "too many row tasks");
+                // one descriptor per kind of work: its units (pad[1]) and quartets
+                auto add = [&](int kind, int units, int64_t nq, size_t lds) {
+                    if (units <= 0) return;
+                    a.nq = (int32_t)nq;
+                    d.pad[1] = units;
+                    const Key key = std::make_tuple(class_id(c.li, c.lj, c.lk, c.ll), f, kind, pr, sel);
+                    byg[key].push_back({c.flops * (double)nq / (double)c.nq, d});
+                    glds[key] = std::max(glds[key], lds);
+                };
+                if (!rows) {
+                    k.tile_off = c.d_tile[pr];
+                    k.split = c.tsplit[pr];
+                    k.steps = c.tsteps[pr];
+                    add(0, c.ntiles[pr], c.nq, 0);
+                    continue;
                 }
-                if (!(kind == 1 || ce.batch[f - 1][pr]))
-                    return fail(JK_EUNSUPPORTED, "class (%d%d|%d%d) has no batched kernel", c.li, c.lj, c.lk, c.ll);
-                const Key key = std::make_tuple(class_id(c.li, c.lj, c.lk, c.ll), f, kind, pr, sel);
-                byg[key].push_back({c.flops, d});
-                if (kind == 1) glds[key] = std::max(glds[key], lds1);
+                k.tshK = c.d_tshK;
+                k.tshL = c.d_tshL;
+                k.ncolK = c.ncolK;
+                k.ncolL = c.ncolL;
+                k.seg_same = c.seg_same;
+                auto place = [&](const std::vector<int32_t> &tasks) {
+                    d.pad[2] = (int32_t)alltasks.size();  // offset into the task buffer (host only)
+                    alltasks.insert(alltasks.end(), tasks.begin(), tasks.end());
+                    return (int)(tasks.size() / 3);
+                };
+                if (wide) {
+                    a.dstage = 1;
+                    const bool dst = f == 1 && k1_dstage(c.li, c.lj, nset, ncols, c.npb);
+                    const int n = place(c.h_rowc[f - 1]);
+                    add(2, n, c.nq_row, dst ? k1_row_lds(c.li, c.lj, nset, ncols, c.npb, true) : lds4);
+                    a.dstage = 0;
+                    const int n2 = place(c.h_srowt);
+                    add(1, n2, c.nq - c.nq_row, lds1);
+                } else {
+                    // every bra of the class: long bras in chunks, short ones whole
+                    std::vector<int32_t> all(c.h_rowc[f - 1]);
+                    all.insert(all.end(), c.h_srowt.begin(), c.h_srowt.end());
+                    add(1, place(all), c.nq, lds1);
+                }
+                if (alltasks.size() > (size_t)INT32_MAX) return fail(JK_EINVAL, "too many row tasks");
             }
         }
     }
@@ -380,12 +403,12 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
         g.kind = std::get<2>(kv.first);
         g.pr = std::get<3>(kv.first);
         g.sel = std::get<4>(kv.first);
-        g.lds = g.kind == 1 ? glds[kv.first] : 0;
+        g.lds = glds[kv.first];
         g.first = (int)b->hdesc.size();
         g.count = (int)v.size();
         int64_t tiles = 0;
         for (auto &x : v) {
-            x.second.tile_base = (int32_t)tiles;
+            x.second.unit_base = (int32_t)tiles;
             tiles += x.second.pad[1];
             g.work += x.first;
             hdesc_tasks.push_back(x.second.pad[1]);
@@ -407,7 +430,7 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
         const Group &g = b->groups[gi];
         for (int k = 0; k < g.count; ++k) {
             BatchDesc &d = b->hdesc[g.first + k];
-            if (g.kind == 1) d.c.row_pos = b->d_tasks + d.pad[2];
+            if (g.kind != 0) d.c.row_pos = b->d_tasks + d.pad[2];
         }
     }
     // persistent form (JK_BATCH_PERSIST=1; off by default: measured slower

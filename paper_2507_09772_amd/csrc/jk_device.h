@@ -616,6 +616,24 @@ __device__ __forceinline__ void add_count(const JkArgs &a, const ClsArgs &c, int
         atomicAdd(&a.nsel[((size_t)c.ctr * NSEL_SLOTS + blockIdx.x % NSEL_SLOTS) * NSEL_STRIDE], (unsigned long long)n);
 }
 
+// One class of one molecule in a batched build; its units start at unit_base.
+struct BatchDesc {
+    JkArgs a;
+    ClsArgs c;
+    int32_t unit_base;
+    int32_t pad[3];
+};
+
+__device__ __forceinline__ int batch_desc(const BatchDesc *__restrict__ d, int n, int g) {
+    int lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (d[mid].unit_base <= g) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
 // The class of a launch's unit g (uniform in the wave); g becomes the unit
 // within that class.  One launch covers the classes of an angular class:
 // their tiles and row tasks fill the device together, where one launch each
@@ -625,16 +643,42 @@ __device__ __forceinline__ void add_count(const JkArgs &a, const ClsArgs &c, int
 // 374 -> 366 ms).  The class block is
 // written before the launch and only read by kernels, so it is read through
 // the constant address space (scalar loads, a field where it is used).
-__device__ __forceinline__ const ClsArgs &group_class(const ClsArgs *cls, const ClsGroup &grp, int &g) {
-    int lo = 0, hi = grp.n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (grp.base[mid] <= g) lo = mid;
-        else hi = mid - 1;
-    }
-    g -= grp.base[lo];
+// Batched builds launch the same kernels over the classes of many molecules
+// (descs), heaviest first, each descriptor with its molecule's arguments.  The
+// single build's arguments are the kernel's first, at the start of its
+// argument segment.  Family 1 reads both there, through the constant address
+// space: a field is loaded where it is used, where a by-value copy held the
+// block in registers (74 -> 26 spilled scalar registers in (ps|ps)).  Families 2
+// and 3 copy the arguments once: read in place, the reloads in their inner
+// loops cost up to 50 % ((gf|fp) tiles 15.7 -> 23.4 ms, (dp|pp) rows 15.2 -> 18.9).
+struct Work {
+    const JkArgs &a;
+    const ClsArgs &c;
+};
+__device__ __forceinline__ Work find_work(const ClsArgs *cls, const ClsGroup &grp, const BatchDesc *descs, int ndesc, int &g) {
+    using CArgs = const __attribute__((address_space(4))) JkArgs;
     using CCls = const __attribute__((address_space(4))) ClsArgs;
-    return *(const ClsArgs *)&((CCls *)cls)[grp.desc[lo]];
+    using CDesc = const __attribute__((address_space(4))) BatchDesc;
+    CArgs *pa;
+    CCls *pc;
+    if (descs) {
+        const int m = __builtin_amdgcn_readfirstlane(batch_desc(descs, ndesc, g));
+        CDesc *d = &((CDesc *)descs)[m];
+        g -= d->unit_base;
+        pa = &d->a;
+        pc = &d->c;
+    } else {
+        int lo = 0, hi = grp.n - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (grp.base[mid] <= g) lo = mid;
+            else hi = mid - 1;
+        }
+        g -= grp.base[lo];
+        pa = (CArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+        pc = &((CCls *)cls)[grp.desc[lo]];
+    }
+    return Work{*(const JkArgs *)pa, *(const ClsArgs *)pc};
 }
 
 __device__ __forceinline__ double pair_weight(int bra, int ket, const PairRec &B, const PairRec &K) {
@@ -1060,12 +1104,13 @@ __device__ __forceinline__ void k1_tile(const JkArgs &a, const ClsArgs &c, int w
 
 // Tiles: one wave per tile of 64 kets of one bra.
 template <int LI, int LJ, int LK, int LL, typename R, int MODE>
-__global__ void __launch_bounds__(256) jk_k1(const JkArgs a, const ClsArgs *__restrict__ cls, const ClsGroup grp) {
+__global__ void __launch_bounds__(256) jk_k1(const JkArgs a, const ClsArgs *__restrict__ cls, const ClsGroup grp,
+                                             const BatchDesc *__restrict__ descs, int ndesc, int units) {
     if constexpr (MODE == MODE_JK) {
         int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-        if (wave >= grp.base[grp.n]) return;
-        const ClsArgs &c = group_class(cls, grp, wave);
-        k1_tile<LI, LJ, LK, LL, R>(a, c, wave);
+        if (wave >= units) return;
+        const Work w = find_work(cls, grp, descs, ndesc, wave);
+        k1_tile<LI, LJ, LK, LL, R>(w.a, w.c, wave);
     } else {
         const int g = blockIdx.x * 256 + threadIdx.x;
         const bool valid = g < a.nq;
@@ -1074,41 +1119,13 @@ __global__ void __launch_bounds__(256) jk_k1(const JkArgs a, const ClsArgs *__re
     }
 }
 
-struct BatchDesc {
-    JkArgs a;
-    ClsArgs c;
-    int32_t tile_base;
-    int32_t pad[3];
-};
-
-// The argument blocks of descriptor m.  The descriptors are written before
-// the launch and only read by the kernels, so they are read through the
-// constant address space: the compiler may then load a field where it is
-// used (and load it again later) instead of holding the whole block in
-// registers, which made the batched family-1 row kernels spill.
-__device__ __forceinline__ const BatchDesc &desc_args(const BatchDesc *descs, int m) {
-    using CDesc = const __attribute__((address_space(4))) BatchDesc;
-    return *(const BatchDesc *)&((CDesc *)descs)[m];
-}
-
-__device__ __forceinline__ int batch_desc(const BatchDesc *__restrict__ d, int n, int g) {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (d[mid].tile_base <= g) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
 // Row mode: one workgroup of NT lanes walks a chunk of one bra's ket prefix
 // (a row task: list position, first and end ket).  K'_IK, K'_IL (row block
 // of shell I) and K'_JK, K'_JL (row block of J) accumulate in LDS over the
 // compressed ket-type columns, J'_IJ in LDS, and only J'_KL leaves per
 // quartet (atomics into the pair-ordered buffer).  Dynamic LDS layout: the bra's npb primitive pair
 // records, then per density [NI rows | NJ rows] x ncols and NAB for J'_IJ.
-// NT = 256 for long bras, 64 for short ones;
-// BATCH: the task indexes the row tasks of many descriptors (molecules).
+// NT = 256 for long bras, 64 for short ones.
 template <int LI, int LJ, int LK, int LL, typename R, int NT>
 __device__ __forceinline__ void k1_row_task(const JkArgs &a, const ClsArgs &c, int task) {
     using C = Cls<LI, LJ, LK, LL>;
@@ -1327,19 +1344,13 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, const ClsArgs &c, i
 constexpr int k1_row_waves(int li, int lj, int lk, int ll, int rsize) {
     return (li + lj + lk + ll == 1 && rsize == 8) ? 5 : 1;
 }
-template <int LI, int LJ, int LK, int LL, typename R, int NT, bool BATCH>
+template <int LI, int LJ, int LK, int LL, typename R, int NT>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(k1_row_waves(LI, LJ, LK, LL, sizeof(R)))))
-jk_k1_row(const JkArgs a, const ClsArgs *__restrict__ cls, const ClsGroup grp, const BatchDesc *__restrict__ descs,
+jk_k1_row(const JkArgs, const ClsArgs *__restrict__ cls, const ClsGroup grp, const BatchDesc *__restrict__ descs,
           int ndesc) {
     int task = blockIdx.x;
-    if constexpr (BATCH) {
-        const int m = __builtin_amdgcn_readfirstlane(batch_desc(descs, ndesc, task));
-        const BatchDesc &d = desc_args(descs, m);
-        k1_row_task<LI, LJ, LK, LL, R, NT>(d.a, d.c, task - d.tile_base);
-    } else {
-        const ClsArgs &c = group_class(cls, grp, task);
-        k1_row_task<LI, LJ, LK, LL, R, NT>(a, c, task);
-    }
+    const Work w = find_work(cls, grp, descs, ndesc, task);
+    k1_row_task<LI, LJ, LK, LL, R, NT>(w.a, w.c, task);
 }
 
 // ===========================================================================
@@ -1774,7 +1785,8 @@ __device__ __forceinline__ void k2_body(const JkArgs &a, R *tabs, double *dig, i
     } while (0)
 
 template <int LI, int LJ, int LK, int LL, typename R, int MODE>
-__global__ void __launch_bounds__(k2_lanes(LI, LJ, LK, LL)) jk_k2(const JkArgs a, const ClsArgs *__restrict__ cls, const ClsGroup grp) {
+__global__ void __launch_bounds__(k2_lanes(LI, LJ, LK, LL)) jk_k2(const JkArgs a, const ClsArgs *__restrict__ cls, const ClsGroup grp,
+                                                                        const BatchDesc *__restrict__ descs, int ndesc) {
     using F = K2Cfg<LI, LJ, LK, LL, false>;
     constexpr int QW = F::QW, LPQ = F::LPQ;
     __shared__ R tabs[QW * F::TAB];
@@ -1785,9 +1797,10 @@ __global__ void __launch_bounds__(k2_lanes(LI, LJ, LK, LL)) jk_k2(const JkArgs a
     const bool lane_used = q < QW;
     const int qq = lane_used ? q : 0;
     if constexpr (MODE == MODE_JK) {
-        int wave = (int)blockIdx.x;
-        const ClsArgs &c = group_class(cls, grp, wave);
-        JK_K2_TILE(a, c, wave);
+        int tile = (int)blockIdx.x;
+        const Work w = find_work(cls, grp, descs, ndesc, tile);
+        const JkArgs args = w.a;
+        JK_K2_TILE(args, w.c, tile);
     } else {
         const int gq = blockIdx.x * QW + qq;
         const bool valid = lane_used && gq < a.nq;
@@ -1815,8 +1828,8 @@ struct K2RowLds {
 // (The body stays in the kernel itself: behind one more inlined function
 // layer hipcc moved the (ff|ff) FP64 accumulators to scratch and the kernel
 // returned wrong values, as with the tile prologue.)
-template <int LI, int LJ, int LK, int LL, typename R, int NT, bool BATCH>
-__global__ void __launch_bounds__(NT) jk_k2_row(const JkArgs a_in, const ClsArgs *__restrict__ cls, const ClsGroup grp,
+template <int LI, int LJ, int LK, int LL, typename R, int NT>
+__global__ void __launch_bounds__(NT) jk_k2_row(const JkArgs, const ClsArgs *__restrict__ cls, const ClsGroup grp,
                                                 const BatchDesc *__restrict__ descs, int ndesc) {
     using C = Cls<LI, LJ, LK, LL>;
     using F = K2Cfg<LI, LJ, LK, LL, true>;
@@ -1824,13 +1837,10 @@ __global__ void __launch_bounds__(NT) jk_k2_row(const JkArgs a_in, const ClsArgs
     constexpr int QW = F::QW, LPQ = F::LPQ, NW = NT / 64;
     extern __shared__ double smem2[];
     const int tid = threadIdx.x, wave = tid >> 6, lane = lane_index();
-    int task = blockIdx.x, m = 0;
-    if constexpr (BATCH) {
-        m = __builtin_amdgcn_readfirstlane(batch_desc(descs, ndesc, task));
-        task -= desc_args(descs, m).tile_base;
-    }
-    const JkArgs &a = BATCH ? desc_args(descs, m).a : a_in;
-    const ClsArgs &c = BATCH ? desc_args(descs, m).c : group_class(cls, grp, task);
+    int task = blockIdx.x;
+    const Work w = find_work(cls, grp, descs, ndesc, task);
+    const JkArgs a = w.a;
+    const ClsArgs &c = w.c;
     const int ncols = c.ncolK + (c.seg_same ? 0 : c.ncolL);
     const int segL = c.seg_same ? 0 : c.ncolK;
     const int per_set = (NI + NJ) * ncols + NAB;
@@ -1999,8 +2009,8 @@ __device__ __forceinline__ void hrr_lane(const R *src, R ab, R cd, R (&T)[(LJ + 
     }
 }
 
-template <int LI, int LJ, int LK, int LL, typename R, int NT, bool BATCH>
-__global__ void __launch_bounds__(NT) jk_k3_row(const JkArgs a_in, const ClsArgs *__restrict__ cls, const ClsGroup grp,
+template <int LI, int LJ, int LK, int LL, typename R, int NT>
+__global__ void __launch_bounds__(NT) jk_k3_row(const JkArgs, const ClsArgs *__restrict__ cls, const ClsGroup grp,
                                                 const BatchDesc *__restrict__ descs, int ndesc) {
     using C = Cls<LI, LJ, LK, LL>;
     using F = K3Cfg<LI, LJ, LK, LL>;
@@ -2008,13 +2018,10 @@ __global__ void __launch_bounds__(NT) jk_k3_row(const JkArgs a_in, const ClsArgs
     constexpr int LPQ = F::LPQ, QW = F::QW, NW = NT / 64, NCC = F::NCC, TS = F::TS, PB = F::PB;
     extern __shared__ double smem3[];
     const int tid = threadIdx.x, wave = tid >> 6, lane = lane_index();
-    int task = blockIdx.x, m = 0;
-    if constexpr (BATCH) {
-        m = __builtin_amdgcn_readfirstlane(batch_desc(descs, ndesc, task));
-        task -= desc_args(descs, m).tile_base;
-    }
-    const JkArgs &a = BATCH ? desc_args(descs, m).a : a_in;
-    const ClsArgs &c = BATCH ? desc_args(descs, m).c : group_class(cls, grp, task);
+    int task = blockIdx.x;
+    const Work w = find_work(cls, grp, descs, ndesc, task);
+    const JkArgs a = w.a;
+    const ClsArgs &c = w.c;
     const int ncols = c.ncolK + (c.seg_same ? 0 : c.ncolL);
     const int segL = c.seg_same ? 0 : c.ncolK;
     const int per_set = (NI + NJ) * ncols + NAB;
@@ -2231,39 +2238,6 @@ __global__ void __launch_bounds__(NT) jk_k3_row(const JkArgs a_in, const ClsArgs
             atomic_add_f64(&Km[row * n + col], v);
         }
     }
-}
-
-// ===========================================================================
-// Batched builds: one launch per (class, family) covers the tiles of every
-// molecule of the batch.  Global tile g belongs to the descriptor m with
-// tile_base[m] <= g < tile_base[m + 1]; each descriptor holds the JkArgs of
-// one (molecule, class task), heaviest first, so the dispatcher hands out
-// the long tiles early.
-// ===========================================================================
-template <int LI, int LJ, int LK, int LL, typename R>
-__global__ void __launch_bounds__(256) jk_k1_batch(const BatchDesc *__restrict__ descs, int ndesc, int total) {
-    const int g = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-    if (g >= total) return;
-    const int m = __builtin_amdgcn_readfirstlane(batch_desc(descs, ndesc, g));
-    const BatchDesc &d = desc_args(descs, m);
-    k1_tile<LI, LJ, LK, LL, R>(d.a, d.c, g - d.tile_base);
-}
-
-template <int LI, int LJ, int LK, int LL, typename R>
-__global__ void __launch_bounds__(k2_lanes(LI, LJ, LK, LL)) jk_k2_batch(const BatchDesc *__restrict__ descs, int ndesc, int total) {
-    using F = K2Cfg<LI, LJ, LK, LL, false>;
-    constexpr int QW = F::QW, LPQ = F::LPQ;
-    __shared__ R tabs[QW * F::TAB];
-    __shared__ double dig[F::DIGW];
-    const int lane = threadIdx.x;
-    const int q = QW > 1 ? lane / LPQ : 0;
-    const int sl = QW > 1 ? lane % LPQ : lane;
-    const bool lane_used = q < QW;
-    const int qq = lane_used ? q : 0;
-    const int g = blockIdx.x;
-    const int m = __builtin_amdgcn_readfirstlane(batch_desc(descs, ndesc, g));
-    const BatchDesc &d = desc_args(descs, m);
-    JK_K2_TILE(d.a, d.c, g - d.tile_base);
 }
 
 }  // namespace jk

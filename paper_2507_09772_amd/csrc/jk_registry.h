@@ -10,12 +10,14 @@ constexpr int LMAX_BUILT = 4;  // classes instantiated up to (gg|gg)
 
 // Export of an explicit quartet list.
 using ExportLauncher = hipError_t (*)(const JkArgs &, hipStream_t);
-// One launch over the tiles (lds unused) or row tasks (lds: the largest
-// workgroup need) of a group of classes.
-using Launcher = hipError_t (*)(const JkArgs &, const ClsArgs *, const ClsGroup &, size_t lds, hipStream_t);
-// Batched builds: the tiles of many descriptors (molecules) in one launch.
-using BatchLauncher = hipError_t (*)(const BatchDesc *, int ndesc, int total_tiles, hipStream_t);
-using BatchRowLauncher = hipError_t (*)(const BatchDesc *, int ndesc, int total_tasks, size_t lds, hipStream_t);
+// One launch over the units (tiles, lds unused; or row tasks, lds the largest
+// workgroup need) of a group of classes of one build, or of the descriptors
+// of a batch (the first three arguments then unused).
+struct Batch {
+    const BatchDesc *descs = nullptr;
+    int ndesc = 0;
+};
+using Launcher = hipError_t (*)(const JkArgs &, const ClsArgs *, const ClsGroup &, const Batch &, int units, size_t lds, hipStream_t);
 
 struct ClassEntry {
     Launcher tiles[3][2];  // [family - 1][0: FP64, 1: FP32], quartets from tiles (none for family 3)
@@ -23,8 +25,6 @@ struct ClassEntry {
     Launcher row[3][2];    // row mode, 256-lane workgroups (long bras), [family - 1][0: FP64, 1: FP32]
     Launcher srow[3][2];   // row mode, 64-lane workgroups (short bras)
     size_t row_fixed[3][2];  // row-mode LDS bytes per wave besides the K rows, [family - 1][precision]
-    BatchLauncher batch[3][2];       // [family - 1][precision]
-    BatchRowLauncher batch_row[3][2];  // 64-lane row tasks of many descriptors
 };
 
 // LDS bytes of one row-mode workgroup of nw waves: the fixed part (per wave;
