@@ -277,7 +277,16 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
     // Mixed precision: two descriptors per (molecule, class), the
     // single-precision pass over the quartets below the threshold and the
     // double-precision pass over the rest.
-    using Key = std::tuple<int, int, int, int, int>;  // class, family, kind, precision, selection
+    using Key = std::tuple<int, int, int, int, int, int>;  // class, family, kind, precision, selection, LDS size
+    // Rows of different molecules need very different LDS, and a launch gives
+    // every workgroup the largest: descriptors share one where that costs none
+    // of them workgroups per CU (up to 4 of 256 lanes or 16 of 64, beyond which
+    // the registers bind; 48 molecules of 1 to 8 waters: 215 -> 203 ms).
+    auto lds_size = [](int kind, size_t lds) {
+        if (lds == 0) return 0;
+        const int most = kind == 2 ? 4 : 16, wgs = std::min<int>(most, (int)(160 * 1024 / lds));
+        return wgs <= 4 ? wgs : wgs < 8 ? 6 : wgs < 12 ? 8 : wgs < 16 ? 12 : 16;
+    };
     std::map<Key, std::vector<std::pair<double, BatchDesc>>> byg;
     std::vector<int32_t> alltasks;
     std::map<Key, size_t> glds;
@@ -352,7 +361,7 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                     if (units <= 0) return;
                     a.nq = (int32_t)nq;
                     d.pad[1] = units;
-                    const Key key = std::make_tuple(class_id(c.li, c.lj, c.lk, c.ll), f, kind, pr, sel);
+                    const Key key = std::make_tuple(class_id(c.li, c.lj, c.lk, c.ll), f, kind, pr, sel, lds_size(kind, lds));
                     byg[key].push_back({c.flops * (double)nq / (double)c.nq, d});
                     glds[key] = std::max(glds[key], lds);
                 };
