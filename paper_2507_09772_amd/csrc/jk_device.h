@@ -1338,11 +1338,17 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, const ClsArgs &c, i
     }
 }
 
-// Waves per SIMD the compiler is held to for a family-1 row kernel: five
-// for the FP64 (ps|ss) class (96 VGPRs; left to itself it takes 101, four
-// waves), none otherwise.
+// Waves per SIMD the compiler is held to for a family-1 FP64 row kernel where
+// the registers it takes by itself are a few over a wave more and the spills
+// stay out of the primitive loop: (ps|ss) five (101 VGPRs otherwise), (ds|ss)
+// four (135; 32 waters basis B 11.7 -> 11.1 ms), (fs|ss) three (190; 7.2 -> 6.8),
+// (ds|ds) two (274; 6.1 -> 4.9) and (dp|ps) two (290; 19.8 -> 19.1).  Measured and
+// left: (pp|ps) three 14.9 -> 21.9 ms, (dp|ss) three 7.5 -> 9.5, (fp|ss) two 7.4 -> 8.2.
 constexpr int k1_row_waves(int li, int lj, int lk, int ll, int rsize) {
-    return (li + lj + lk + ll == 1 && rsize == 8) ? 5 : 1;
+    if (rsize != 8) return 1;
+    const int id = class_id(li, lj, lk, ll);
+    return id == class_id(1, 0, 0, 0) ? 5 : id == class_id(2, 0, 0, 0) ? 4 : id == class_id(3, 0, 0, 0) ? 3
+           : id == class_id(2, 0, 2, 0) || id == class_id(2, 1, 1, 0) ? 2 : 1;
 }
 template <int LI, int LJ, int LK, int LL, typename R, int NT>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(k1_row_waves(LI, LJ, LK, LL, sizeof(R)))))
