@@ -43,6 +43,12 @@ static int launch_counts(const jk_plan *P, std::vector<int64_t> *out);
 // most chunk kets of one bra (by default row_chunk of the family; a set
 // value applies to the row tasks of every family).
 static const int ROW_MIN_KETS = 192;
+// ... and from 64 (one wave's) in classes of at least ROW_SHORT_QUARTETS: a
+// tile sends its K blocks through global atomics, a row keeps them in LDS, which
+// pays as soon as a wave is full; below, the tiles' shared quartets fill the
+// device better.
+static const int ROW_MIN_KETS_LARGE = 64;
+static const int64_t ROW_SHORT_QUARTETS = 16384;
 static int32_t g_minkets[NCLS];
 static int32_t g_chunk[NCLS];
 // Mixed-precision split per class: 0 default (split), 1 split, 2 the whole
@@ -827,8 +833,8 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
                 c.d_tshL = d_tsh[tL];
                 std::vector<int32_t> rows, sb, scn;
                 for (size_t i = 0; i < bl.size(); ++i) {
-                    const int minkets = g_minkets[class_id(c.li, c.lj, c.lk, c.ll)] > 0
-                                            ? g_minkets[class_id(c.li, c.lj, c.lk, c.ll)] : ROW_MIN_KETS;
+                    const int set = g_minkets[class_id(c.li, c.lj, c.lk, c.ll)];
+                    const int minkets = set > 0 ? set : c.nq >= ROW_SHORT_QUARTETS ? ROW_MIN_KETS_LARGE : ROW_MIN_KETS;
                     if (cn[i] >= minkets) {
                         rows.push_back((int32_t)i);
                         c.nq_row += cn[i];

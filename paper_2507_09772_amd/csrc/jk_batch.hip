@@ -383,13 +383,22 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                     return (int)(tasks.size() / 3);
                 };
                 if (wide) {
+                    // (a task of fewer than 192 kets leaves a wave of the four idle)
+                    std::vector<int32_t> longs, shorts(c.h_srowt);
+                    int64_t nq_long = 0;
+                    for (size_t t = 0; t < c.h_rowc[f - 1].size(); t += 3) {
+                        const int32_t *v = c.h_rowc[f - 1].data() + t;
+                        std::vector<int32_t> &to = v[2] - v[1] >= 192 ? longs : shorts;
+                        to.insert(to.end(), v, v + 3);
+                        if (v[2] - v[1] >= 192) nq_long += v[2] - v[1];
+                    }
                     a.dstage = 1;
                     const bool dst = f == 1 && k1_dstage(c.li, c.lj, nset, ncols, c.npb);
-                    const int n = place(c.h_rowc[f - 1]);
-                    add(2, n, c.nq_row, dst ? k1_row_lds(c.li, c.lj, nset, ncols, c.npb, true) : lds4);
+                    const int n = place(longs);
+                    add(2, n, nq_long, dst ? k1_row_lds(c.li, c.lj, nset, ncols, c.npb, true) : lds4);
                     a.dstage = 0;
-                    const int n2 = place(c.h_srowt);
-                    add(1, n2, c.nq - c.nq_row, lds1);
+                    const int n2 = place(shorts);
+                    add(1, n2, c.nq - nq_long, lds1);
                 } else {
                     // every bra of the class: long bras in chunks, short ones whole
                     std::vector<int32_t> all(c.h_rowc[f - 1]);
