@@ -251,8 +251,9 @@ int jk_boys_eval(int32_t m, const double *T_host, int32_t count, int32_t precisi
 /*
  * Per-kernel timing (measurement support).  While enabled, jk_execute
  * launches every class kernel on its stream, one after another, records a
- * HIP event on that stream before and after every class-kernel launch, waits for the last one before returning, and adds each launch's
- * duration to the running total of its (class, precision, kind) entry.
+ * HIP event on that stream before and after every class-kernel launch, waits
+ * for the last one before returning, and adds each launch's duration to the
+ * running total of its (class, precision, kind) entry.
  * jk_plan_profile(plan, 1) resets the totals; jk_plan_timings copies up to
  * cap entries (those that ran) and stores the number available in *count.
  */
@@ -289,7 +290,8 @@ int jk_plan_timings(const jk_plan *plan, jk_class_timing *out, int32_t cap, int3
  * short ones in 64-lane workgroups): in row mode a workgroup walks (a chunk
  * of) one bra's ket prefix and keeps the bra's K rows in LDS, so most J/K
  * updates stay out of global atomics; batched builds run every bra of a
- * class as 64-lane row tasks unless its setting is 2.  At load time the
+ * class as row tasks unless its setting is 2, the long ones in 256-lane
+ * workgroups where row mode is allowed, the others in 64.  At load time the
  * library reads tune_gfx950.txt next to itself (or the file named by
  * JK_TUNE_DB): one "li lj lk ll precision family [row]" line per entry,
  * "shape ..." lines (jk_tune_set_shape), '#' comments.
@@ -302,7 +304,8 @@ int jk_tune_get(int32_t li, int32_t lj, int32_t lk, int32_t ll, int32_t precisio
                 int32_t *available);
 /* Task shape of one class (the fragmentation of Section 3.2), read by plans
  * created afterwards: bras with at least min_kets kets run in row mode
- * (default 192) and one row task covers at most chunk kets of a bra (default:
+ * (default 64 in contraction classes of 4096 quartets and more, 192 in
+ * smaller ones) and one row task covers at most chunk kets of a bra (default:
  * 2048 for family 1, 256 wave steps for families 2 and 3); 0 restores a
  * default.  Table lines "shape li lj lk ll min_kets chunk". */
 int jk_tune_set_shape(int32_t li, int32_t lj, int32_t lk, int32_t ll, int32_t min_kets, int32_t chunk);

@@ -35,8 +35,8 @@ sys.path.insert(0, os.path.dirname(HERE))
 
 OUT = os.path.join(HERE, "tune_gfx950.txt")
 ROWNAME = {1: "row", 2: "tile", 3: "allrow"}
-# shape grid: (min_kets, chunk scale against the family default)
-SHAPES = [(m, s) for m in (96, 192, 384) for s in (0.5, 1.0, 2.0)]
+# shape grid: (min_kets, 0 for the default; chunk scale against the family default)
+SHAPES = [(m, s) for m in (0, 96, 384) for s in (0.5, 1.0, 2.0)]
 
 
 def default_chunk(fam, li):
@@ -115,7 +115,7 @@ def main():
     lines = ["# kernel family per (class, precision), chosen by paper_2507_09772_amd/autotune.py",
              f"# workloads: {' '.join(args.workloads)}; columns: li lj lk ll precision(0 fp64, 2 fp32) family "
              "row(1 long bras, 2 off, 3 all bras)",
-             "# shape lines: li lj lk ll min_kets chunk (the long-bra threshold and kets per row task)",
+             "# shape lines: li lj lk ll min_kets chunk (the long-bra threshold, 0 the default, and kets per row task)",
              "# split lines: li lj lk ll 0 (the class runs in double precision in mixed builds)"]
     report = {}
     choice = {}
@@ -155,11 +155,11 @@ def main():
             if not opts:
                 continue
             (mk, sc), best = min(opts.items(), key=lambda kv: kv[1])
-            base = opts.get((192, 1.0), best)
+            base = opts.get((0, 1.0), best)
             fam = choice.get((c, "fp64"), (1, 1))[0]
             print(f"shape ({c[0]}{c[1]}|{c[2]}{c[3]}): best min_kets {mk} chunk x{sc} {best:.3f} ms "
                   f"(default {base:.3f} ms)", flush=True)
-            if (mk, sc) != (192, 1.0) and best < 0.97 * base:
+            if (mk, sc) != (0, 1.0) and best < 0.97 * base:
                 lines.append(f"shape {c[0]} {c[1]} {c[2]} {c[3]} {mk} {int(default_chunk(fam, c[0]) * sc)}")
             report[f"shape ({c[0]}{c[1]}|{c[2]}{c[3]})"] = {f"m{k[0]}x{k[1]}": v for k, v in opts.items()}
     split, rs = split_lines(jk, synth, torch, args.workloads)

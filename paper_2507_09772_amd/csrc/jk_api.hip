@@ -39,16 +39,20 @@ static void ensure_tuning();
 static int launch_counts(const jk_plan *P, std::vector<int64_t> *out);
 
 // Task shape per class (host side; 0 = default): bras with at least
-// min_kets kets run in row mode (the default 192), and a row task covers at
-// most chunk kets of one bra (by default row_chunk of the family; a set
-// value applies to the row tasks of every family).
+// min_kets kets run in row mode, and a row task covers at most chunk kets of
+// one bra (by default row_chunk of the family; a set value applies to the row
+// tasks of every family).  The default min_kets is 64 (one wave's) in
+// contraction classes of at least ROW_LARGE_QUARTETS quartets: a tile sends its
+// K blocks through global atomics, a row keeps them in LDS, which pays as soon
+// as a wave is full (ms per FP64 build with 192 everywhere, then with the line
+// at 16384 and at 4096 quartets: 24 waters, basis A 6.15, 5.4, 5.2; 7 waters,
+// basis B 10.1, 9.8, 7.7; 32, 48 and 96 kets and lines at 1024, 2048 and 8192
+// were slower on some molecule).  Smaller classes leave the device idle, and
+// there tiles, whose quartets can share lanes, are faster until a row's four
+// waves are well filled: 192.
 static const int ROW_MIN_KETS = 192;
-// ... and from 64 (one wave's) in classes of at least ROW_SHORT_QUARTETS: a
-// tile sends its K blocks through global atomics, a row keeps them in LDS, which
-// pays as soon as a wave is full; below, the tiles' shared quartets fill the
-// device better.
 static const int ROW_MIN_KETS_LARGE = 64;
-static const int64_t ROW_SHORT_QUARTETS = 16384;
+static const int64_t ROW_LARGE_QUARTETS = 4096;
 static int32_t g_minkets[NCLS];
 static int32_t g_chunk[NCLS];
 // Mixed-precision split per class: 0 default (split), 1 split, 2 the whole
@@ -834,7 +838,7 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
                 std::vector<int32_t> rows, sb, scn;
                 for (size_t i = 0; i < bl.size(); ++i) {
                     const int set = g_minkets[class_id(c.li, c.lj, c.lk, c.ll)];
-                    const int minkets = set > 0 ? set : c.nq >= ROW_SHORT_QUARTETS ? ROW_MIN_KETS_LARGE : ROW_MIN_KETS;
+                    const int minkets = set > 0 ? set : c.nq >= ROW_LARGE_QUARTETS ? ROW_MIN_KETS_LARGE : ROW_MIN_KETS;
                     if (cn[i] >= minkets) {
                         rows.push_back((int32_t)i);
                         c.nq_row += cn[i];

@@ -4,7 +4,7 @@
 // Every molecule keeps its own plan (pairs, sorted ket lists, tiles).  The
 // batch gathers, per angular class and kernel family, the class tasks of all
 // molecules into one descriptor array; one launch per group covers the
-// tiles of all its descriptors, heaviest molecule first.  The
+// tiles or row tasks of all its descriptors, heaviest molecule first.  The
 // basis transforms, clearing and finalisation run as batched kernels with
 // one grid row per molecule.  The whole sequence is recorded once into a
 // hipGraph and replayed on every call.

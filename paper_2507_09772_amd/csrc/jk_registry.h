@@ -10,13 +10,14 @@ constexpr int LMAX_BUILT = 4;  // classes instantiated up to (gg|gg)
 
 // Export of an explicit quartet list.
 using ExportLauncher = hipError_t (*)(const JkArgs &, hipStream_t);
-// One launch over the units (tiles, lds unused; or row tasks, lds the largest
-// workgroup need) of a group of classes of one build, or of the descriptors
-// of a batch (the first three arguments then unused).
+// Descriptors of one launch of a batched build (none: a single build).
 struct Batch {
     const BatchDesc *descs = nullptr;
     int ndesc = 0;
 };
+// One launch over the units (tiles, lds unused; or row tasks, lds the largest
+// workgroup need) of a group of classes of one build, or of the descriptors
+// of a batch (the first three arguments then unused).
 using Launcher = hipError_t (*)(const JkArgs &, const ClsArgs *, const ClsGroup &, const Batch &, int units, size_t lds, hipStream_t);
 
 struct ClassEntry {
