@@ -20,13 +20,24 @@ LIB = os.path.join(HERE, "libjk.so")
 LMAX_BUILT = 4
 BRAS = [(i, j) for i in range(LMAX_BUILT + 1) for j in range(i + 1)]
 
+# -amdgpu-spill-vgpr-to-agpr=0: spilled registers go to scratch as a whole.  By
+# default the compiler puts a spilled 64-bit value's halves in a spare AGPR and
+# in scratch where it can.  Reloading such a value into an AGPR pair it emits
+#   aN+1 = COPY aM, implicit-def aN_aN+1;  aN = scratch load, implicit-def aN_aN+1
+# and its copy propagation takes the second definition of the pair for a new
+# value of both halves and deletes the copy: the high half keeps whatever the
+# pair held before.  One family-1 row kernel ((fp|ds), single precision) used
+# such a pair for an integral in its loop over the densities, and returned wrong
+# J and K for all densities after the first.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-munsafe-fp-atomics",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"]
 # the kernel units also print each kernel's resource usage, checked below
 RESOURCE_FLAGS = ["-Rpass-analysis=kernel-resource-usage"]
 # Private memory (scratch) per lane.  Two family-2 (ff|ff) kernels once
 # returned wrong values at 2736 and 2848 bytes per lane, while the same
-# classes at about 800 bytes were right; the cause was not found.  So every
+# classes at about 800 bytes were right; their code is not there any more to
+# tell whether the lost halves above were the cause.  So every
 # kernel that spills is held to the scratch size recorded in KNOWN_GOOD (the
 # sizes of the build whose kernels passed the parity tests on the device),
 # and a kernel missing from that record to SCRATCH_LIMIT: a build whose

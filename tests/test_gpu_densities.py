@@ -1,0 +1,81 @@
+"""Two densities through every kernel: each class forced to each family it is
+built for, as 256-lane rows (bras from 4 kets), 64-lane rows and tiles, in FP64
+and FP32, against the oracle.  The block of a quartet has to survive the
+digestion of the first density for the second one.
+
+FP32 tolerance: the single-precision roots are good to 3e-6, a Cartesian
+integral is a product of three recurrences of them and at most Q_ij Q_kl large,
+and a spherical one a combination of some ten of them: an element of J is off
+by no more than 1e-4 Q_ij sum_kl Q_kl |D_kl|, and one of K by 1e-4 sum_jl Q_ij
+|D_jl| Q_kl.  (A lost register half shows at the size of the integrals.)
+"""
+import os
+
+import numpy as np
+import pytest
+
+from oracle import oracle as o
+from paper_2507_09772_amd import synth
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-10  # the repository's FP64 bar
+ROWS = {"rows": (1, 4), "rows64": (3, 1 << 20), "tiles": (2, 0)}  # row setting, min_kets
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+
+    from paper_2507_09772_amd import jk
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    torch.cuda.init()
+    return torch, jk
+
+
+@pytest.fixture(scope="module")
+def reference():
+    out = {}
+    for basis, nw in (("B", 3), ("C", 1)):
+        wl = synth.small_workload(nw, basis, seed=930, nset=2)
+        out[basis] = (wl, *o.jk(wl.mol, wl.D, wl.cutoff, mode=1)[:2])
+    return out
+
+
+@pytest.mark.parametrize("form", sorted(ROWS))
+@pytest.mark.parametrize("fam", [1, 2, 3])
+@pytest.mark.parametrize("basis", ["B", "C"])
+def test_two_densities(env, reference, basis, fam, form):
+    torch, jk = env
+    wl, J0, K0 = reference[basis]
+    row, minkets = ROWS[form]
+    print("two densities", basis, fam, form, flush=True)
+    try:
+        for c in jk.canonical_classes():
+            jk.tune_set_shape(*c, minkets, 0)
+            jk.tune_set_split(*c, 1)
+            for p in ("fp64", "fp32"):
+                _, avail = jk.tune_get(*c, p)
+                jk.tune_set(*c, p, fam if avail & (1 << (fam - 1)) else 0)
+                jk.tune_set_row(*c, p, row)
+        plan = jk.Plan(wl.mol, wl.cutoff)
+        D = torch.from_numpy(wl.D).cuda()
+        # Schwarz factors per function
+        nf = [2 * l + 1 if wl.mol.spherical else (l + 1) * (l + 2) // 2 for l in wl.mol.l]
+        Q = np.repeat(np.repeat(plan.schwarz(), nf, 0), nf, 1)
+        for prec in ("fp64", "mixed", "fp32"):
+            J, K = plan.execute(D, precision=prec)
+            torch.cuda.synchronize()
+            for s in range(2):
+                A = np.abs(wl.D[s])
+                dj, dk = np.abs(J[s].cpu().numpy() - J0[s]), np.abs(K[s].cpu().numpy() - K0[s])
+                tj, tk = (TOL, TOL) if prec == "fp64" else (TOL + 1e-4 * Q * (Q * A).sum(), TOL + 1e-4 * Q @ A @ Q)
+                assert (dj <= tj).all() and (dk <= tk).all(), (prec, s, dj.max(), dk.max())
+        plan.close()
+    finally:
+        for c in jk.canonical_classes():
+            jk.tune_set_shape(*c, 0, 0)
+            jk.tune_set_split(*c, 1)
+            for p in ("fp64", "fp32"):
+                jk.tune_set(*c, p, 0)
+                jk.tune_set_row(*c, p, 0)
+        jk.tune_load(os.path.join(os.path.dirname(jk.__file__), "tune_gfx950.txt"))
