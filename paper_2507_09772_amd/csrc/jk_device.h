@@ -1131,11 +1131,6 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, const ClsArgs &c, i
     using C = Cls<LI, LJ, LK, LL>;
     constexpr int NI = C::NI, NJ = C::NJ, NK = C::NK, NL = C::NL, NAB = C::NAB, NCD = C::NCD;
     extern __shared__ double rowmem[];
-    // Blocks of more than 110 elements: lanes without a quartet go through the
-    // digestion with weight zero instead of being masked.  Masked, the values
-    // of the block that are spilled inside were wrong for the next density
-    // in one such kernel ((fp|ds) in single precision, 256 lanes).
-    constexpr bool BIG = C::NC > 110;
     const int tid = threadIdx.x, lane = lane_index();
     const int i = c.row_pos[3 * task];
     const int jbeg = c.row_pos[3 * task + 1], cnt = c.row_pos[3 * task + 2];
@@ -1216,19 +1211,18 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, const ClsArgs &c, i
 #pragma unroll
                 for (int m = 0; m < NM; ++m)
                     if (lane + 64 * m < NAB) atomicAdd(&jij[lane + 64 * m], mine[m]);
-                if (BIG || valid) {
+                if (valid) {
                     double *jq = a.jp + s * a.jpstride + Kt.jp_off;
 #pragma unroll
                     for (int cd2 = 0; cd2 < NCD; ++cd2) {
                         double s2 = 0.0;
 #pragma unroll
                         for (int ab2 = 0; ab2 < NAB; ++ab2) s2 += (double)V[ab2 * NCD + cd2] * dij[ab2];
-                        if (!BIG || valid) atomic_add_f64(&jq[(int64_t)cd2 * Kt.pp_stride], w2 * s2);
+                        atomic_add_f64(&jq[(int64_t)cd2 * Kt.pp_stride], w2 * s2);
                     }
                 }
             }
-            if (a.do_k && (BIG || valid)) {
-                const double wk = valid ? wq : 0.0;
+            if (a.do_k && valid) {
                 double djl[NJ * NL], djk[NJ * NK], dil[NI * NL], dik[NI * NK];
                 if (dstage) {
                     const double *dr = drows + s * dper;
@@ -1272,7 +1266,7 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, const ClsArgs &c, i
 #pragma unroll
                             for (int l = 0; l < NL; ++l)
                                 s2 += (double)V[((i2 * NJ + j2) * NK + k) * NL + l] * djl[j2 * NL + l];
-                        atomicAdd(&rI[i2 * ncols + cK + k], wk * s2);
+                        atomicAdd(&rI[i2 * ncols + cK + k], wq * s2);
                     }
 #pragma unroll
                 for (int i2 = 0; i2 < NI; ++i2)
@@ -1284,7 +1278,7 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, const ClsArgs &c, i
 #pragma unroll
                             for (int k = 0; k < NK; ++k)
                                 s2 += (double)V[((i2 * NJ + j2) * NK + k) * NL + l] * djk[j2 * NK + k];
-                        atomicAdd(&rI[i2 * ncols + cL + l], wk * s2);
+                        atomicAdd(&rI[i2 * ncols + cL + l], wq * s2);
                     }
 #pragma unroll
                 for (int j2 = 0; j2 < NJ; ++j2)
@@ -1296,7 +1290,7 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, const ClsArgs &c, i
 #pragma unroll
                             for (int l = 0; l < NL; ++l)
                                 s2 += (double)V[((i2 * NJ + j2) * NK + k) * NL + l] * dil[i2 * NL + l];
-                        atomicAdd(&rJ[j2 * ncols + cK + k], wk * s2);
+                        atomicAdd(&rJ[j2 * ncols + cK + k], wq * s2);
                     }
 #pragma unroll
                 for (int j2 = 0; j2 < NJ; ++j2)
@@ -1308,7 +1302,7 @@ __device__ __forceinline__ void k1_row_task(const JkArgs &a, const ClsArgs &c, i
 #pragma unroll
                             for (int k = 0; k < NK; ++k)
                                 s2 += (double)V[((i2 * NJ + j2) * NK + k) * NL + l] * dik[i2 * NK + k];
-                        atomicAdd(&rJ[j2 * ncols + cL + l], wk * s2);
+                        atomicAdd(&rJ[j2 * ncols + cL + l], wq * s2);
                     }
             }
         }

@@ -79,3 +79,47 @@ def test_two_densities(env, reference, basis, fam, form):
                 jk.tune_set(*c, p, 0)
                 jk.tune_set_row(*c, p, 0)
         jk.tune_load(os.path.join(os.path.dirname(jk.__file__), "tune_gfx950.txt"))
+
+
+def test_screened_quartets_leave_no_trace(env):
+    """Density screening drops a quartet before its elements of D are read: D
+    holds values on one water only and a NaN between two shells of another.
+    The NaN reaches K through the evaluated quartets alone, so rows and tiles
+    (forced to family 1, whose lanes are masked one by one) agree on where."""
+    torch, jk = env
+    wl = synth.small_workload(3, "B", seed=931)
+    mol = wl.mol
+    nf = [2 * l + 1 if mol.spherical else (l + 1) * (l + 2) // 2 for l in mol.l]
+    off = np.concatenate([[0], np.cumsum(nf)])
+    atom = np.repeat(np.asarray(mol.atom), nf)
+    oxygens = sorted(set(int(a) for a, l in zip(mol.atom, mol.l) if l == 3))
+    on = atom == oxygens[0]
+    D = np.where(on[:, None] & on[None, :], wl.D, 0.0)
+    f2, d2 = (next(i for i in range(mol.nshell) if mol.atom[i] == oxygens[1] and mol.l[i] == l) for l in (3, 2))
+    D[0, off[f2], off[d2]] = D[0, off[d2], off[f2]] = np.nan
+    out = {}
+    try:
+        for form in ("tiles", "rows"):
+            row, minkets = ROWS[form]
+            for c in jk.canonical_classes():
+                _, avail = jk.tune_get(*c, "fp64")
+                jk.tune_set(*c, "fp64", 1 if avail & 1 else 0)
+                jk.tune_set_row(*c, "fp64", row)
+                jk.tune_set_shape(*c, minkets, 0)
+            plan = jk.Plan(mol, wl.cutoff)
+            plan.set_density_screening(1e-8)
+            print("screened", form, flush=True)
+            _, K = plan.execute(torch.from_numpy(D).cuda(), flags=jk.JK_DO_K)
+            torch.cuda.synchronize()
+            out[form] = K[0].cpu().numpy()
+            plan.close()
+    finally:
+        for c in jk.canonical_classes():
+            jk.tune_set_shape(*c, 0, 0)
+            jk.tune_set(*c, "fp64", 0)
+            jk.tune_set_row(*c, "fp64", 0)
+        jk.tune_load(os.path.join(os.path.dirname(jk.__file__), "tune_gfx950.txt"))
+    nan = np.isnan(out["tiles"])
+    assert 0 < nan.sum() < nan.size
+    assert (np.isnan(out["rows"]) == nan).all()
+    assert np.abs(out["rows"] - out["tiles"])[~nan].max() <= TOL
