@@ -1300,6 +1300,7 @@ int execute_impl(jk_plan *P, const double *D, int32_t nset, int32_t flags, int32
         Launcher fn;
         size_t lds;
         int sel, slot;  // quartet selection; counter slot (timed builds)
+        bool rest;      // not the first part of its class (timed builds)
         double flops;
         ClsGroup g;
     };
@@ -1326,29 +1327,29 @@ int execute_impl(jk_plan *P, const double *D, int32_t nset, int32_t flags, int32
             // into their LDS rows from several waves, in no fixed order)
             const bool tiles_only = sel == SEL_HI || det || P->no_row;
             const size_t first = launches.size();
-            auto add = [&](Launcher fn, size_t ci, int kind, int units, size_t lds, int64_t nq) {
+            // (wg, per: lanes of a workgroup and the units it takes)
+            auto add = [&](Launcher fn, size_t ci, int kind, int wg, int per, int units, size_t lds, int64_t nq) {
                 const int slot = work_slot(ci, pr, kind == WORK_STILES ? WORK_TILES : kind);
                 P->last_fixed[slot] = count_on_device ? -1 : nq;
                 const int wgs = lds ? std::min(8, (int)(160 * 1024 / lds)) : 0;
-                size_t k = first;
-                if (profile) k = launches.size();
-                while (k < launches.size() &&
-                       !(launches[k].fn == fn && launches[k].g.n < GROUP_MAX &&
-                         (lds == 0 || wgs == std::min(8, (int)(160 * 1024 / launches[k].lds))) &&
-                         launches[k].g.base[launches[k].g.n] <= INT32_MAX - units))
-                    ++k;
-                if (k == launches.size()) {
-                    launches.emplace_back();
-                    launches[k].fn = fn;
-                    launches[k].sel = sel;
-                    launches[k].slot = slot;
+                const int64_t max = launch_units_max(wg, per);
+                size_t k = profile ? launches.size() : first;
+                for (int64_t from = 0; from < units; ++k) {
+                    if (k == launches.size()) {
+                        launches.emplace_back();
+                        launches[k].fn = fn;
+                        launches[k].sel = sel;
+                        launches[k].slot = slot;
+                        launches[k].lds = lds;
+                        launches[k].rest = from > 0;
+                    }
+                    Launch &l = launches[k];
+                    if (l.fn != fn || (lds && wgs != std::min(8, (int)(160 * 1024 / l.lds)))) continue;
+                    const int64_t done = from;
+                    if (!group_add(l.g, work_slot(ci, pr, kind), units, max, &from)) continue;
+                    l.lds = std::max(l.lds, lds);
+                    l.flops += P->cls[ci].flops * (double)nq / (double)P->cls[ci].nq * (double)(from - done) / units;
                 }
-                Launch &l = launches[k];
-                l.lds = std::max(l.lds, lds);
-                l.g.desc[l.g.n] = work_slot(ci, pr, kind);
-                l.g.base[l.g.n + 1] = l.g.base[l.g.n] + units;
-                ++l.g.n;
-                l.flops += P->cls[ci].flops * (double)nq / (double)P->cls[ci].nq;
             };
             for (int ci : v) {
                 const ClassTask &c = P->cls[ci];
@@ -1362,13 +1363,14 @@ int execute_impl(jk_plan *P, const double *D, int32_t nset, int32_t flags, int32
                 // (family 1 with the bra's D rows in LDS where they fit)
                 const bool dst = a.dstage && f == 1 && k1_dstage(c.li, c.lj, nset, ncols, c.npb);
                 if (longrows)
-                    add(e.row[f - 1][pr], ci, WORK_ROWS, c.nrowc[f - 1],
+                    add(e.row[f - 1][pr], ci, WORK_ROWS, 256, 1, c.nrowc[f - 1],
                         dst ? k1_row_lds(c.li, c.lj, nset, ncols, c.npb, true) : lds4, c.nq_row);
                 // short bras: one 64-lane workgroup each, or tiles
                 const int64_t nq = longrows ? c.nq - c.nq_row : c.nq;
-                if (shortrows) add(e.srow[f - 1][pr], ci, WORK_SROWS, c.nsrow, lds1, c.nq - c.nq_row);
-                else if (longrows && c.nstiles[pr] > 0) add(e.tiles[ft - 1][pr], ci, WORK_STILES, c.nstiles[pr], 0, nq);
-                else if (!longrows && c.ntiles[pr] > 0) add(e.tiles[ft - 1][pr], ci, WORK_TILES, c.ntiles[pr], 0, nq);
+                const int twg = ft == 1 ? 256 : k2_lanes(c.li, c.lj, c.lk, c.ll), tper = ft == 1 ? 4 : 1;
+                if (shortrows) add(e.srow[f - 1][pr], ci, WORK_SROWS, 64, 1, c.nsrow, lds1, c.nq - c.nq_row);
+                else if (longrows && c.nstiles[pr] > 0) add(e.tiles[ft - 1][pr], ci, WORK_STILES, twg, tper, c.nstiles[pr], 0, nq);
+                else if (!longrows && c.ntiles[pr] > 0) add(e.tiles[ft - 1][pr], ci, WORK_TILES, twg, tper, c.ntiles[pr], 0, nq);
             }
         }
     }
@@ -1428,6 +1430,7 @@ int execute_impl(jk_plan *P, const double *D, int32_t nset, int32_t flags, int32
             const int64_t nq = cnt[slot];
             t.ms += ms;
             t.launches += 1;
+            if (launches[k].rest) continue;
             t.nquartets += nq;
             t.model_flops += c.flops * (double)nq / (double)c.nq;
         }

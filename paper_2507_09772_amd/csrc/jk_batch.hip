@@ -422,12 +422,22 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
         g.pr = std::get<3>(kv.first);
         g.sel = std::get<4>(kv.first);
         g.lds = glds[kv.first];
+        // (a launch holds so many units: the rest goes to another)
+        const int li = g.cid / 125, lj = (g.cid / 25) % 5, lk = (g.cid / 5) % 5, ll = g.cid % 5;
+        const int64_t most = g.kind == 1 ? launch_units_max(64, 1) : g.kind == 2 || g.fam == 1
+                             ? launch_units_max(256, g.kind == 2 ? 1 : 4) : launch_units_max(k2_lanes(li, lj, lk, ll), 1);
+        auto close = [&] {
+            g.count = (int)b->hdesc.size() - g.first;
+            if (g.count > 0) b->groups.push_back(g);
+            g.first = (int)b->hdesc.size();
+            g.total_tiles = 0;
+            g.work = 0.0;
+        };
         g.first = (int)b->hdesc.size();
-        g.count = (int)v.size();
-        int64_t tiles = 0;
         for (auto &x : v) {
-            x.second.unit_base = (int32_t)tiles;
-            tiles += x.second.pad[1];
+            if (g.total_tiles + (int64_t)x.second.pad[1] > most) close();
+            x.second.unit_base = g.total_tiles;
+            g.total_tiles += x.second.pad[1];
             g.work += x.first;
             hdesc_tasks.push_back(x.second.pad[1]);
             dwork.push_back(x.first);
@@ -435,9 +445,7 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
             b->dprec.push_back(g.pr);
             b->hdesc.push_back(x.second);
         }
-        if (tiles > INT32_MAX) return fail(JK_EINVAL, "too many tiles in one class group");
-        g.total_tiles = (int)tiles;
-        b->groups.push_back(g);
+        close();
     }
     std::stable_sort(b->groups.begin(), b->groups.end(), [](const Group &x, const Group &y) { return x.work > y.work; });
     // row tasks to the device

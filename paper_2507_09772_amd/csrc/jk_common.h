@@ -161,6 +161,23 @@ struct ClsGroup {
     int32_t desc[GROUP_MAX];
     int32_t base[GROUP_MAX + 1];
 };
+// Most units of one launch whose workgroups have the given lanes and take per
+// units each: a launch holds at most 2^32 - 1 work-items.
+JK_HD constexpr int64_t launch_units_max(int lanes, int per) { return ((int64_t)1 << 32) / lanes * per - per; }
+// Adds units *from .. units - 1 of class desc to a launch of at most max
+// units, or as many of them as a launch of their own takes, and moves *from
+// past them; false: none fit.  (base[0] is -*from for a class in parts.)
+inline bool group_add(ClsGroup &g, int desc, int64_t units, int64_t max, int64_t *from) {
+    const int64_t room = max - (g.n ? g.base[g.n] : 0), left = units - *from;
+    if (g.n == GROUP_MAX || (g.n > 0 && left > room)) return false;
+    const int64_t take = left < room ? left : room;
+    if (g.n == 0) g.base[0] = -(int32_t)*from;
+    g.desc[g.n] = desc;
+    g.base[g.n + 1] = (int32_t)((g.n ? g.base[g.n] : 0) + take);
+    ++g.n;
+    *from += take;
+    return true;
+}
 
 struct JkArgs {
     const PairRec *pairs;
