@@ -190,14 +190,15 @@ static int record(jk_batch *b) {
         hipLaunchKernelGGL(kb_dmax_all, dim3(nm), dim3(256), 0, s, b->d_mol);
         HIPCHK(hipGetLastError());
     }
-    // fork: the class launches go round-robin (heaviest first) onto the
-    // branch streams, which join before the scatter and finalisation
-    HIPCHK(hipEventRecord(b->fork, s));
-    for (int k = 1; k < b->nbranch; ++k) HIPCHK(hipStreamWaitEvent(b->branch[k], b->fork, 0));
+    // (before the fork: the queues of the persistent form run on the branches)
     if (b->d_pctr) {
         hipLaunchKernelGGL(kb_zero_i32, dim3(1), dim3(64), 0, s, b->d_pctr, 2);
         HIPCHK(hipGetLastError());
     }
+    // fork: the class launches go round-robin (heaviest first) onto the
+    // branch streams, which join before the scatter and finalisation
+    HIPCHK(hipEventRecord(b->fork, s));
+    for (int k = 1; k < b->nbranch; ++k) HIPCHK(hipStreamWaitEvent(b->branch[k], b->fork, 0));
     int br = 0;
     for (int pr = 0; pr < 2; ++pr) {
         const jk_batch::Persist &q = b->persist[pr];
