@@ -339,7 +339,6 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                 k.nbra = c.nbra;
                 k.ket_list = c.d_ket;
                 k.npb = c.npb;
-                        a.nq = (int32_t)c.nq;
                 a.tpos = P->d_tpos;
                 a.aoc = P->maps.aoc;
                 a.D = md.Dc;
@@ -393,8 +392,8 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                         to.insert(to.end(), v, v + 3);
                         if (v[2] - v[1] >= 192) nq_long += v[2] - v[1];
                     }
-                    a.dstage = 1;
-                    const bool dst = f == 1 && k1_dstage(c.li, c.lj, nset, ncols, c.npb);
+                    a.dstage = P->no_dstage ? 0 : 1;
+                    const bool dst = a.dstage && f == 1 && k1_dstage(c.li, c.lj, nset, ncols, c.npb);
                     const int n = place(longs);
                     add(2, n, nq_long, dst ? k1_row_lds(c.li, c.lj, nset, ncols, c.npb, true) : lds4);
                     a.dstage = 0;
