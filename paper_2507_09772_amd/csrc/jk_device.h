@@ -651,6 +651,16 @@ __device__ __forceinline__ int batch_desc(const BatchDesc *__restrict__ d, int n
 // block in registers (74 -> 26 spilled scalar registers in (ps|ps)).  Families 2
 // and 3 copy the arguments once: read in place, the reloads in their inner
 // loops cost up to 50 % ((gf|fp) tiles 15.7 -> 23.4 ms, (dp|pp) rows 15.2 -> 18.9).
+// ArgsFirst<kernel type>: what find_work relies on in the kernels that use it;
+// their launchers assert it.
+template <typename K>
+struct ArgsFirst {
+    static constexpr bool ok = false;
+};
+template <typename... Rest>
+struct ArgsFirst<void (*)(JkArgs, const ClsArgs *, ClsGroup, const BatchDesc *, int, Rest...)> {
+    static constexpr bool ok = true;
+};
 struct Work {
     const JkArgs &a;
     const ClsArgs &c;

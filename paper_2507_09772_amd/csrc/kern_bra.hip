@@ -13,6 +13,7 @@ namespace jk {
 template <int LI, int LJ, int LK, int LL, typename R>
 static hipError_t launch_k1(const JkArgs &a, const ClsArgs *cls, const ClsGroup &g, const Batch &b, int units, size_t,
                             hipStream_t s) {
+    static_assert(ArgsFirst<decltype(&jk_k1<LI, LJ, LK, LL, R, MODE_JK>)>::ok, "find_work reads the arguments' start");
     if (units <= 0) return hipSuccess;
     hipLaunchKernelGGL((jk_k1<LI, LJ, LK, LL, R, MODE_JK>), dim3((units + 3) / 4), dim3(256), 0, s, a, cls, g, b.descs, b.ndesc,
                        units);
@@ -38,6 +39,7 @@ static hipError_t lds_opt_in(K kernel, size_t lds, bool &done) {
 
 // Row tasks with one of the row kernels.
 #define JK_LAUNCH_ROW(kernel)                                                                                     \
+    static_assert(ArgsFirst<decltype(&kernel<LI, LJ, LK, LL, R, NT>)>::ok, "find_work reads the arguments' start"); \
     if (units <= 0) return hipSuccess;                                                                            \
     if (lds > (size_t)ROW_LDS_MAX) return hipErrorInvalidValue;                                                   \
     static bool opted_in = false;                                                                                 \
@@ -67,6 +69,7 @@ static hipError_t launch_row3(const JkArgs &a, const ClsArgs *cls, const ClsGrou
 template <int LI, int LJ, int LK, int LL, typename R>
 static hipError_t launch_k2(const JkArgs &a, const ClsArgs *cls, const ClsGroup &g, const Batch &b, int units, size_t,
                             hipStream_t s) {
+    static_assert(ArgsFirst<decltype(&jk_k2<LI, LJ, LK, LL, R, MODE_JK>)>::ok, "find_work reads the arguments' start");
     if (units <= 0) return hipSuccess;
     hipLaunchKernelGGL((jk_k2<LI, LJ, LK, LL, R, MODE_JK>), dim3(units), dim3(k2_lanes(LI, LJ, LK, LL)), 0, s, a, cls, g, b.descs,
                        b.ndesc);
