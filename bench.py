@@ -24,7 +24,9 @@ kernel) for the per-kernel breakdown and the dominant kernel's roofline.
 Errors are taken against the oracle's stored values (tests/golden/, written
 by the oracle alone).  The CPU oracle is timed on a bounded sample.
 
-Prints one JSON line.
+Prints one JSON line, kept to a few kilobytes (figures to five digits; the
+kernels of each build go to stderr), so that a reader of the output's end has
+the whole of it.
 """
 from __future__ import annotations
 
@@ -486,6 +488,19 @@ def cpu_baseline(wl, target_s: float):
                       f"({full_s:.0f} s per build)"}
 
 
+def compact(x):
+    """x without its per-kernel lists, floats to five significant digits, and
+    of each build's roofline the kernel, its rate and fraction."""
+    if isinstance(x, dict):
+        x = {k: compact(v) for k, v in x.items() if k != "top_kernels"}
+        if isinstance(x.get("roofline"), dict):
+            x["roofline"] = {k: x["roofline"].get(k) for k in ("kernel", "achieved", "frac")}
+        return x
+    if isinstance(x, (list, tuple)):
+        return [compact(v) for v in x]
+    return float(f"{x:.5g}") if isinstance(x, float) else x
+
+
 def main():
     ap = argparse.ArgumentParser(description=__doc__, formatter_class=argparse.RawDescriptionHelpFormatter)
     ap.add_argument("--gpus", type=int, default=1)
@@ -504,7 +519,7 @@ def main():
     ap.add_argument("--dscreen", type=float, default=1e-10, help="density screening threshold")
     ap.add_argument("--cpu-seconds", type=float, default=15.0)
     ap.add_argument("--mix-threshold", type=float, default=1e-4)
-    ap.add_argument("--top", type=int, default=12, help="kernels listed per build")
+    ap.add_argument("--top", type=int, default=6, help="kernels listed per build")
     ap.add_argument("--copy-calibration", type=int, default=0, metavar="MIB",
                     help="only run a plain device copy of MIB MiB (scales the HBM counters)")
     args = ap.parse_args()
@@ -569,6 +584,9 @@ def main():
     if not args.no_cpu_baseline:
         log("cpu baseline ...")
         out["cpu_baseline"] = cpu_baseline(synth.workload("c1"), args.cpu_seconds)
+    for k in ("roofline", "configs", "cpu_baseline"):
+        if k in out:
+            out[k] = compact(out[k])
     print(json.dumps(out), flush=True)
 
 
