@@ -106,7 +106,15 @@ struct Group {
     size_t lds;        // row tasks: largest dynamic LDS over the descriptors
     int first, count;
     int total_tiles;
-    double work;       // model FLOPs of the group, for launch order
+    double work;       // model FLOPs of the group
+    double longest;    // model FLOPs of a unit (largest over the descriptors)
+    // What the launch takes, for the order and the branches: its work at the
+    // device's rate, or one unit's chain, which runs at about a thousandth of
+    // it (a wave's rate), where the launch has few units.  By work alone the
+    // long chains of small batches met on one branch: 3 molecules of 1 to 2
+    // waters 2.1 against 1.8 ms, 8 molecules of 1 to 4 waters and four
+    // densities 7.5 against 7.1 (round-robin 2.3 and 7.8).
+    double length() const { return work + 1e3 * longest; }
 };
 
 }  // namespace
@@ -195,10 +203,12 @@ static int record(jk_batch *b) {
         hipLaunchKernelGGL(kb_zero_i32, dim3(1), dim3(64), 0, s, b->d_pctr, 2);
         HIPCHK(hipGetLastError());
     }
-    // fork: the class launches go round-robin (heaviest first) onto the
-    // branch streams, which join before the scatter and finalisation
+    // fork: the class launches go onto the branch streams, longest first, each
+    // to the least loaded one; they join before the scatter and finalisation
     HIPCHK(hipEventRecord(b->fork, s));
     for (int k = 1; k < b->nbranch; ++k) HIPCHK(hipStreamWaitEvent(b->branch[k], b->fork, 0));
+    double load[jk_batch::MAXBRANCH] = {};
+    auto least = [&] { return (int)(std::min_element(load, load + b->nbranch) - load); };
     int br = 0;
     for (int pr = 0; pr < 2; ++pr) {
         const jk_batch::Persist &q = b->persist[pr];
@@ -206,10 +216,11 @@ static int record(jk_batch *b) {
             HIPCHK(launch_k1_persist(pr, b->d_desc, q.items, q.nitems, b->d_pctr + pr, q.lds, q.grid,
                                      b->branch[br++ % b->nbranch]));
     }
-    for (size_t gi = 0; gi < b->groups.size(); ++gi) {
-        const Group &g = b->groups[gi];
+    for (const Group &g : b->groups) {
         const ClassEntry &e = g_classes[g.cid];
-        hipStream_t bs = b->branch[(br + gi) % b->nbranch];
+        const int to = least();
+        load[to] += g.length();
+        hipStream_t bs = b->branch[to];
         const Launcher fn = (g.kind == 0 ? e.tiles : g.kind == 1 ? e.srow : e.row)[g.fam - 1][g.pr];
         HIPCHK(fn(JkArgs{}, nullptr, ClsGroup{}, Batch{b->d_desc + g.first, g.count}, g.total_tiles, g.lds, bs));
     }
@@ -280,14 +291,18 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
     // double-precision pass over the rest.
     using Key = std::tuple<int, int, int, int, int, int>;  // class, family, kind, precision, selection, LDS size
     // Rows of different molecules need very different LDS, and a launch gives
-    // every workgroup the largest: descriptors share one where that costs none
-    // of them workgroups per CU (up to 4 of 256 lanes or 16 of 64, beyond which
-    // the registers bind; 48 molecules of 1 to 8 waters: 215 -> 203 ms).
+    // every workgroup the largest: descriptors are first put together by the
+    // workgroups per CU that their LDS allows (up to 4 of 256 lanes or 16 of 64,
+    // beyond which the registers bind; of 64 lanes 5 to 7, 8 to 11 and 12 to 15
+    // count as one), so that a launch of many workgroups loses few places to
+    // its largest (48 molecules of 1 to 8 waters: 215 -> 203 ms).
     auto lds_size = [](int kind, size_t lds) {
         if (lds == 0) return 0;
         const int most = kind == 2 ? 4 : 16, wgs = std::min<int>(most, (int)(160 * 1024 / lds));
         return wgs <= 4 ? wgs : wgs < 8 ? 6 : wgs < 12 ? 8 : wgs < 16 ? 12 : 16;
     };
+    int ncu = 0;
+    HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
     std::map<Key, std::vector<std::pair<double, BatchDesc>>> byg;
     std::vector<int32_t> alltasks;
     std::map<Key, size_t> glds;
@@ -318,7 +333,8 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                 const int pr = msplit ? (pass == 0 ? 1 : 0) : (precision == JK_FP32 ? 1 : 0);
                 const int sel = msplit ? (pass == 0 ? SEL_LO : SEL_HI) : SEL_ALL;
                 int f = c.fam[pr];
-                const ClassEntry &ce = g_classes[class_id(c.li, c.lj, c.lk, c.ll)];
+                const int cid = class_id(c.li, c.lj, c.lk, c.ll);
+                const ClassEntry &ce = g_classes[cid];
                 const int ncols = c.ncolK + (c.seg_same ? 0 : c.ncolL);
                 const size_t lds1 = row_lds_bytes(ce, f, pr, c.li, c.lj, nset, ncols, 1, c.npb);
                 const size_t lds4 = row_lds_bytes(ce, f, pr, c.li, c.lj, nset, ncols, 4, c.npb);
@@ -361,7 +377,7 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                     if (units <= 0) return;
                     a.nq = (int32_t)nq;
                     d.pad[1] = units;
-                    const Key key = std::make_tuple(class_id(c.li, c.lj, c.lk, c.ll), f, kind, pr, sel, lds_size(kind, lds));
+                    const Key key = std::make_tuple(cid, f, kind, pr, sel, lds_size(kind, lds));
                     byg[key].push_back({c.flops * (double)nq / (double)c.nq, d});
                     glds[key] = std::max(glds[key], lds);
                 };
@@ -409,6 +425,33 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
             }
         }
     }
+    // A launch whose workgroups all have a place on the device twice over at
+    // most takes as long as its longest ones, whatever its LDS, and a launch
+    // more is as long again: LDS sizes of one kernel go together up to there
+    // (ms per batch by the places up to which they do: 0, 1, 2, 4; 8 molecules
+    // of 1 to 4 waters, four densities: 10.7, 8.6, 7.8, 7.9; 20 such molecules,
+    // two densities: 11.9, 11.1, 10.6, 10.5; 48 molecules of 1 to 8 waters, four
+    // densities: 202, 200, 204, 200).
+    for (auto it = byg.begin(); it != byg.end();) {
+        const auto kernel = [](const Key &k) {
+            return std::make_tuple(std::get<0>(k), std::get<1>(k), std::get<2>(k), std::get<3>(k), std::get<4>(k));
+        };
+        auto end = it;
+        size_t lds = 1;
+        int64_t units = 0;
+        for (; end != byg.end() && kernel(end->first) == kernel(it->first); ++end) {
+            lds = std::max(lds, glds[end->first]);
+            for (const auto &d : end->second) units += d.second.pad[1];
+        }
+        const int64_t places = ncu * (int64_t)std::min<size_t>(std::get<2>(it->first) == 2 ? 4 : 16, 160 * 1024 / lds);
+        const auto first = it++;
+        if (units <= 2 * places)
+            for (; it != end; it = byg.erase(it)) {
+                first->second.insert(first->second.end(), it->second.begin(), it->second.end());
+                glds[first->first] = lds;
+            }
+        it = end;
+    }
     std::vector<int32_t> hdesc_tasks;  // work units per descriptor
     std::vector<double> dwork;         // model FLOPs per descriptor
     std::vector<int32_t> dclass;       // class id per descriptor
@@ -431,7 +474,7 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
             if (g.count > 0) b->groups.push_back(g);
             g.first = (int)b->hdesc.size();
             g.total_tiles = 0;
-            g.work = 0.0;
+            g.work = g.longest = 0.0;
         };
         g.first = (int)b->hdesc.size();
         for (auto &x : v) {
@@ -439,6 +482,7 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
             x.second.unit_base = g.total_tiles;
             g.total_tiles += x.second.pad[1];
             g.work += x.first;
+            g.longest = std::max(g.longest, x.first / x.second.pad[1]);
             hdesc_tasks.push_back(x.second.pad[1]);
             dwork.push_back(x.first);
             dclass.push_back(g.cid);
@@ -447,7 +491,7 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
         }
         close();
     }
-    std::stable_sort(b->groups.begin(), b->groups.end(), [](const Group &x, const Group &y) { return x.work > y.work; });
+    std::stable_sort(b->groups.begin(), b->groups.end(), [](const Group &x, const Group &y) { return x.length() > y.length(); });
     // row tasks to the device
     if ((rc = b->alloc(&b->d_tasks, alltasks.size()))) return rc;
     if (!alltasks.empty())
@@ -502,8 +546,6 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
         d.pad[1] = d.pad[2] = 0;
     }
     if ((rc = b->alloc(&b->d_desc, b->hdesc.size())) || (rc = b->alloc(&b->d_mol, nmol))) return rc;
-    int ncu = 0;
-    HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
     for (int pr = 0; pr < 2; ++pr) {
         auto &v = pitems[pr];
         if (v.empty()) continue;
