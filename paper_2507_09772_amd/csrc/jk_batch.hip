@@ -301,8 +301,17 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
         const int most = kind == 2 ? 4 : 16, wgs = std::min<int>(most, (int)(160 * 1024 / lds));
         return wgs <= 4 ? wgs : wgs < 8 ? 6 : wgs < 12 ? 8 : wgs < 16 ? 12 : 16;
     };
+    // The double-precision pass of a mixed split evaluates the first few kets
+    // of each bra.  A class with fewer bras in all molecules than the device has
+    // SIMDs runs it as tiles, as single builds do (8 molecules of 1 to 4 waters
+    // 7.7 -> 7.3 ms with four densities, 2.4 -> 2.0 with one); with more, rows
+    // keep their K blocks out of global atomics (48 molecules of 1 to 8 waters
+    // 91.9 ms as tiles, 85.2 as rows).
     int ncu = 0;
     HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+    std::vector<int64_t> nbras(NCLS, 0);
+    for (int m = 0; m < nmol; ++m)
+        for (const ClassTask &c : plans[m]->cls) nbras[class_id(c.li, c.lj, c.lk, c.ll)] += c.nbra;
     std::map<Key, std::vector<std::pair<double, BatchDesc>>> byg;
     std::vector<int32_t> alltasks;
     std::map<Key, size_t> glds;
@@ -338,7 +347,8 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
                 const int ncols = c.ncolK + (c.seg_same ? 0 : c.ncolL);
                 const size_t lds1 = row_lds_bytes(ce, f, pr, c.li, c.lj, nset, ncols, 1, c.npb);
                 const size_t lds4 = row_lds_bytes(ce, f, pr, c.li, c.lj, nset, ncols, 4, c.npb);
-                const bool rows = c.row_ok[pr] && ce.srow[f - 1][pr] && lds1 <= (size_t)ROW_LDS_MAX;
+                const bool rows = c.row_ok[pr] && ce.srow[f - 1][pr] && lds1 <= (size_t)ROW_LDS_MAX &&
+                                  !(sel == SEL_HI && nbras[cid] <= 4 * ncu);
                 const bool wide = rows && !c.h_rowc[f - 1].empty() && lds4 <= (size_t)ROW_LDS_MAX;
                 // tiles of a family-3 class run in its fallback family
                 if (!rows) f = c.tile_family(pr);

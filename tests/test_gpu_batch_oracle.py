@@ -57,3 +57,34 @@ def test_batch(env, staged):
                 tj, tk = (TOL, TOL) if prec == "fp64" else (TOL + 1e-4 * Q * (Q * A).sum(), TOL + 1e-4 * Q @ A @ Q)
                 assert (dj <= tj).all() and (dk <= tk).all(), (prec, w.name, s, dj.max(), dk.max())
         b.close()
+
+
+@pytest.mark.parametrize("copies", [2, 40])
+def test_copies(env, copies):
+    """The same molecule 2 and 40 times: launches that leave the device idle (the
+    LDS sizes of a kernel together, the double-precision pass as tiles) and ones
+    that fill it (apart, rows); every copy against the oracle."""
+    torch, jk, wls, ref = env
+    w, (J0, K0) = wls[3], ref[3]
+    a, (Ja, Ka) = wls[0], ref[0]
+    plan, small = jk.Plan(w.mol, w.cutoff), jk.Plan(a.mol, a.cutoff)
+    D, d = torch.from_numpy(w.D).cuda(), torch.from_numpy(a.D).cuda()
+    Ds = [D, d] * copies
+    for prec in ("fp64", "mixed"):
+        print("copies", prec, copies, flush=True)
+        Js, Ks = ([torch.full_like(x, np.nan) for x in Ds] for _ in range(2))
+        b = jk.Batch([plan, small] * copies, nset=3, precision=prec)
+        b.execute(Ds, Js, Ks)
+        torch.cuda.synchronize()
+        n, n32 = b.stats()
+        assert n == copies * (plan.stats().nquartets + small.stats().nquartets)
+        nf = [2 * l + 1 for l in w.mol.l]
+        Q = np.repeat(np.repeat(plan.schwarz(), nf, 0), nf, 1)
+        A = np.abs(w.D)
+        tj, tk = ((TOL, TOL) if prec == "fp64" else
+                  (TOL + 1e-4 * Q * np.einsum("kl,skl->s", Q, A)[:, None, None], TOL + 1e-4 * Q @ A @ Q))
+        for J, K in zip(Js[::2], Ks[::2]):
+            assert (np.abs(J.cpu().numpy() - J0) <= tj).all() and (np.abs(K.cpu().numpy() - K0) <= tk).all(), (prec, copies)
+        for J, K in zip(Js[1::2], Ks[1::2]):
+            assert np.abs(J.cpu().numpy() - Ja).max() <= 1e-9 and np.abs(K.cpu().numpy() - Ka).max() <= 1e-9
+        b.close()
