@@ -36,7 +36,7 @@ struct PairRec {
     int32_t ish, jsh;      // shell indices
     int32_t aoi, aoj;      // Cartesian AO offsets
     int32_t pp_off, npp;   // first primitive pair, count (those that matter in
-                           // double precision, largest first)
+                           // double precision, smallest first)
     int32_t pp_stride;     // distance between its consecutive primitive pairs
                            // (= the number of pairs of its type)
     int32_t jp_off;        // its first element in the pair-ordered J' buffer;
