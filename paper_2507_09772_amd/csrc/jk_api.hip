@@ -531,7 +531,7 @@ static int place_classes(jk_plan *P) {
     return P->put(&P->d_cls, ca);
 }
 
-extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **out) {
+static int plan_create_impl(const jk_basis *basis, double cutoff, jk_plan **out) {
     if (!out) return fail(JK_EINVAL, "out is NULL");
     ensure_tuning();
     *out = nullptr;
@@ -927,6 +927,10 @@ extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **ou
     return JK_OK;
 }
 
+extern "C" int jk_plan_create(const jk_basis *basis, double cutoff, jk_plan **out) {
+    return entry([&] { return plan_create_impl(basis, cutoff, out); });
+}
+
 extern "C" void jk_plan_destroy(jk_plan *plan) { delete plan; }
 
 extern "C" int jk_plan_info(const jk_plan *P, int32_t *nao, int32_t *nao_cart) {
@@ -936,7 +940,7 @@ extern "C" int jk_plan_info(const jk_plan *P, int32_t *nao, int32_t *nao_cart) {
     return 0;
 }
 
-extern "C" int jk_plan_stats(const jk_plan *P, jk_stats *st) {
+static int plan_stats_impl(const jk_plan *P, jk_stats *st) {
     if (!P || !st) return fail(JK_EINVAL, "NULL argument");
     *st = P->stats;
     st->nquartets_fp32 = 0;
@@ -953,6 +957,10 @@ extern "C" int jk_plan_stats(const jk_plan *P, jk_stats *st) {
         }
     }
     return 0;
+}
+
+extern "C" int jk_plan_stats(const jk_plan *P, jk_stats *st) {
+    return entry([&] { return plan_stats_impl(P, st); });
 }
 
 // ---------------------------------------------------------------------------
@@ -1462,11 +1470,13 @@ int execute_impl(jk_plan *P, const double *D, int32_t nset, int32_t flags, int32
 
 extern "C" int jk_execute(jk_plan *P, const double *D, int32_t nset, int32_t flags, int32_t precision, double mix_threshold,
                           double omega, double *J, double *K, void *stream) {
-    int rc = check_execute_args(P, D, nset, flags, precision, mix_threshold, omega, J, K);
-    if (rc) return rc;
-    Scratch sc;
-    if ((rc = ensure_scratch(P, nset, &sc, (flags & JK_DETERMINISTIC) != 0))) return rc;
-    return execute_impl(P, D, nset, flags, precision, mix_threshold, omega, J, K, (hipStream_t)stream, sc, true);
+    return entry([&] {
+        int rc = check_execute_args(P, D, nset, flags, precision, mix_threshold, omega, J, K);
+        if (rc) return rc;
+        Scratch sc;
+        if ((rc = ensure_scratch(P, nset, &sc, (flags & JK_DETERMINISTIC) != 0))) return rc;
+        return execute_impl(P, D, nset, flags, precision, mix_threshold, omega, J, K, (hipStream_t)stream, sc, true);
+    });
 }
 
 extern "C" int jk_plan_set_density_screening(jk_plan *P, double threshold) {
@@ -1476,7 +1486,7 @@ extern "C" int jk_plan_set_density_screening(jk_plan *P, double threshold) {
     return JK_OK;
 }
 
-extern "C" int jk_plan_profile(jk_plan *P, int32_t enable) {
+static int plan_profile_impl(jk_plan *P, int32_t enable) {
     if (!P) return fail(JK_EINVAL, "plan is NULL");
     P->profile = enable != 0;
     P->timing.assign(8 * P->cls.size(), jk_class_timing{});
@@ -1493,6 +1503,10 @@ extern "C" int jk_plan_profile(jk_plan *P, int32_t enable) {
                 t.kind = kind;
             }
     return 0;
+}
+
+extern "C" int jk_plan_profile(jk_plan *P, int32_t enable) {
+    return entry([&] { return plan_profile_impl(P, enable); });
 }
 
 extern "C" int jk_plan_timings(const jk_plan *P, jk_class_timing *out, int32_t cap, int32_t *count) {
@@ -1521,7 +1535,7 @@ extern "C" int jk_build(const jk_basis *basis, const double *D, int32_t nset, do
     return rc;
 }
 
-extern "C" int jk_eri_block(jk_plan *P, int32_t I, int32_t J, int32_t K, int32_t L, int32_t precision, double *host_out) {
+static int eri_block_impl(jk_plan *P, int32_t I, int32_t J, int32_t K, int32_t L, int32_t precision, double *host_out) {
     if (!P || !host_out) return fail(JK_EINVAL, "NULL argument");
     const int ns = P->ns;
     if (I < 0 || J < 0 || K < 0 || L < 0 || I >= ns || J >= ns || K >= ns || L >= ns) return fail(JK_EINVAL, "shell index out of range");
@@ -1580,6 +1594,10 @@ extern "C" int jk_eri_block(jk_plan *P, int32_t I, int32_t J, int32_t K, int32_t
                         blk[idx[0] * strides[0] + idx[1] * strides[1] + idx[2] * strides[2] + idx[3] * strides[3]];
                 }
     return 0;
+}
+
+extern "C" int jk_eri_block(jk_plan *P, int32_t I, int32_t J, int32_t K, int32_t L, int32_t precision, double *host_out) {
+    return entry([&] { return eri_block_impl(P, I, J, K, L, precision, host_out); });
 }
 
 extern "C" int jk_rys_eval(int32_t n, const double *T, int32_t count, int32_t precision, double *roots, double *weights) {

@@ -235,8 +235,8 @@ static int record(jk_batch *b) {
     return 0;
 }
 
-extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset, int32_t precision,
-                               double mix_threshold, jk_batch **out) {
+static int batch_create_impl(jk_plan *const *plans, int32_t nmol, int32_t nset, int32_t precision,
+                             double mix_threshold, jk_batch **out) {
     if (!out) return fail(JK_EINVAL, "out is NULL");
     *out = nullptr;
     if (!plans || nmol < 1 || nmol > 65535) return fail(JK_EINVAL, "need 1 <= nmol <= 65535 plans");
@@ -597,7 +597,12 @@ extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset
     return JK_OK;
 }
 
-extern "C" int jk_batch_execute(jk_batch *b, const double *const *D, double *const *J, double *const *K, void *stream) {
+extern "C" int jk_batch_create(jk_plan *const *plans, int32_t nmol, int32_t nset, int32_t precision,
+                               double mix_threshold, jk_batch **out) {
+    return entry([&] { return batch_create_impl(plans, nmol, nset, precision, mix_threshold, out); });
+}
+
+static int batch_execute_impl(jk_batch *b, const double *const *D, double *const *J, double *const *K, void *stream) {
     if (!b) return fail(JK_EINVAL, "batch is NULL");
     if (!D || !J || !K) return fail(JK_EINVAL, "D, J and K pointer arrays must be non-NULL");
     int dev = 0;
@@ -641,7 +646,11 @@ extern "C" int jk_batch_execute(jk_batch *b, const double *const *D, double *con
     return JK_OK;
 }
 
-extern "C" int jk_batch_stats(const jk_batch *b, int64_t *nquartets, int64_t *nquartets_fp32) {
+extern "C" int jk_batch_execute(jk_batch *b, const double *const *D, double *const *J, double *const *K, void *stream) {
+    return entry([&] { return batch_execute_impl(b, D, J, K, stream); });
+}
+
+static int batch_stats_impl(const jk_batch *b, int64_t *nquartets, int64_t *nquartets_fp32) {
     if (!b) return fail(JK_EINVAL, "batch is NULL");
     const size_t per = (size_t)NSEL_SLOTS * NSEL_STRIDE;
     std::vector<unsigned long long> raw(b->hdesc.size() * per);
@@ -661,6 +670,10 @@ extern "C" int jk_batch_stats(const jk_batch *b, int64_t *nquartets, int64_t *nq
     if (nquartets) *nquartets = n;
     if (nquartets_fp32) *nquartets_fp32 = n32;
     return JK_OK;
+}
+
+extern "C" int jk_batch_stats(const jk_batch *b, int64_t *nquartets, int64_t *nquartets_fp32) {
+    return entry([&] { return batch_stats_impl(b, nquartets, nquartets_fp32); });
 }
 
 extern "C" void jk_batch_destroy(jk_batch *b) { delete b; }

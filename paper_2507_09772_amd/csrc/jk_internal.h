@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "../../include/jk.h"
+#include "jk_guard.h"
 #include "jk_registry.h"
 
 using namespace jk;
@@ -18,6 +19,15 @@ using namespace jk;
 // Error reporting: fail() stores a thread-local message and returns code.
 extern thread_local std::string g_err;
 int fail(int code, const char *fmt, ...);
+
+// An entry point's body: out of host memory is a status, not an exception.
+template <typename F>
+int entry(F &&body) noexcept {
+    return guarded(body, [] {
+        g_err.clear();
+        return JK_ENOMEM;
+    });
+}
 
 #define HIPCHK(expr)                                                                   \
     do {                                                                               \
