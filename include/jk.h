@@ -107,7 +107,7 @@ typedef struct {
                                    contraction lengths */
     int64_t nquartets_fp32;     /* quartets the last build ran in FP32 (JK_MIXED: those
                                    below the threshold; JK_FP32: all evaluated) */
-    int32_t nclasses;           /* (bra pair type, ket pair type) launches */
+    int32_t nclasses;           /* contraction classes (bra pair type, ket pair type) */
     int32_t npairs;             /* shell pairs kept after screening */
     double setup_ms;            /* jk_plan_create wall time */
     double model_flops;         /* algorithmic FLOPs of one build with nset = 1, over the

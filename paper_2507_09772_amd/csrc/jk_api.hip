@@ -270,10 +270,6 @@ __global__ void k_schwarz(const double *blocks, int nab, const int32_t *pair_ids
     pairs[pair_ids[t]].q = sqrt(m);
 }
 
-__global__ void k_fill_i32(int32_t *p, int n) {
-    for (int t = threadIdx.x; t < n; t += blockDim.x) p[t] = 0;
-}
-
 // The fixed-order limbs of elements 0..n-1 (limbs L apart) into doubles, in
 // place over the first limb: the smallest part first, the same order for
 // every element and every build.

@@ -525,9 +525,9 @@ __device__ __forceinline__ double swap_add(double x, double y) {
     return __longlong_as_double((long long)p) + __longlong_as_double((long long)q);
 }
 // Sums of N values over the wave, all lanes active: add(e, sum of v[e]) is
-// called by one lane per element.  The values are halved twice by lane swaps (a quarter of them is left per row of
-// 16 lanes) and then rotated within the rows: about five vector instructions
-// per value and no LDS traffic, against twelve LDS permutes and six additions
+// called by one lane per element.  The values are halved twice by lane swaps
+// (a quarter of them is left per row of 16 lanes) and then rotated within the
+// rows: about five vector instructions per value and no LDS traffic, against twelve LDS permutes and six additions
 // of a butterfly over each value.
 template <int N, typename Add>
 __device__ __forceinline__ void wave_sums(double (&v)[N], Add &&add) {
@@ -1830,9 +1830,6 @@ struct K2RowLds {
     // per wave of the workgroup
     template <typename R>
     static constexpr size_t fixed() { return (size_t)F::DIGW * sizeof(double) + (size_t)F::QW * F::TAB * sizeof(R); }
-    static constexpr size_t per_set(int ncols) {
-        return sizeof(double) * ((size_t)(ncart(LI) + ncart(LJ)) * ncols + (size_t)ncart(LI) * ncart(LJ));
-    }
 };
 
 // (The body stays in the kernel itself: behind one more inlined function
@@ -1955,9 +1952,6 @@ struct K3Cfg {
     static constexpr int JW = QW * C::NK * C::NL;
     template <typename R>
     static constexpr size_t wave_bytes() { return (size_t)JW * sizeof(double) + (size_t)GW * sizeof(R); }
-    static constexpr size_t per_set(int ncols) {
-        return sizeof(double) * ((size_t)(C::NI + C::NJ) * ncols + (size_t)C::NI * C::NJ);
-    }
 };
 
 // Vertical recurrence of one direction and root: G(n, m), n <= NA, m <= NC,

@@ -224,7 +224,7 @@ struct jk_plan {
     // per-kernel timing
     bool profile = false;
     std::vector<hipEvent_t> events;
-    std::vector<jk_class_timing> timing;  // [(2 * class + (FP32 ? 1 : 0)) * 3 + kind]
+    std::vector<jk_class_timing> timing;  // [work_slot(class, precision, kind)]
 
     template <typename T>
     int alloc(T **p, size_t n) {
