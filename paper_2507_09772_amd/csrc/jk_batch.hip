@@ -593,6 +593,10 @@ static int batch_create_impl(jk_plan *const *plans, int32_t nmol, int32_t nset, 
         HIPCHK(hipEventCreateWithFlags(&b->join[k], hipEventDisableTiming));
     }
     HIPCHK(hipEventCreateWithFlags(&b->fork, hipEventDisableTiming));
+    // the tasks and descriptors are on the device before any stream runs the
+    // batch (a copy from pageable memory may return before its last transfer,
+    // and a non-blocking stream does not wait for the null stream)
+    HIPCHK(hipStreamSynchronize(nullptr));
     *out = b.release();
     return JK_OK;
 }
